@@ -155,7 +155,10 @@ int lsms_build_liz_subset(lsms_ctx* ctx, int32_t n_atoms, const double* pos, con
  * refinement's residual reads (2176 bytes per pair; no FP64 copy of M is kept), solution and
  * residual blocks (npad x 32 complex128 each) and the pivots.  Systems recomputed in FP64 take
  * the wave's matrix area once their FP32 factors are done with (a wave of one system borrows
- * a buffer for its FP64 matrix).
+ * a buffer for its FP64 matrix).  Beside the workspace the context keeps the scratch of the
+ * tournament panels and, in split mode, at most 1 GiB per stream (or one system's share, 4100
+ * npad bytes, if that is more) for the operand pairs of the wide updates; without memory for those
+ * the updates run on the FP32 matrix cores.
  * An atom whose LIZ is empty (liz_ptr[a + 1] == liz_ptr[a]) is skipped: no system is
  * solved for it and its info and berr are 0 (not allowed with keep).  This lets a
  * caller solve a subset of a structure's atoms with the structure's phase array.
@@ -298,8 +301,11 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * the streaming persistent form, whose next tile's first K chunk is loaded during the current
  * tile's last one, without and with the C tile loaded early; 19: as 2 with each job's tiles
  * numbered in bands of eight tile rows, so one XCD's resident workgroups share few L21 and
- * U12 panels in its L2; 20: as 13 in bands of eight tile rows); every
- * tiling computes the same update (results may differ in FP32 rounding order only).  Host-side setting of the context, no device work; returns
+ * U12 panels in its L2, and, for wide updates of at least 512 rows, the FP16 matrix cores with every
+ * FP32 operand as a scaled pair of FP16 numbers and FP32 sums; 20: as 13 in bands of eight tile rows); every
+ * tiling computes the same update (the FP32 tilings differ in rounding order only; 19's pairs hold
+ * the operands to 2^-24 of their value and round its sums less often: its error against FP64 is
+ * the smaller one).  Host-side setting of the context, no device work; returns
  * LSMS_E_ARG for an unknown knob or value.  lsms_get_tuning reports the tiling in effect.
  */
 #define LSMS_TUNE_GEMM_F32 0

@@ -406,16 +406,21 @@ int gemm_f32_variants_all() { return gemm_f32_variants() + 11; }
 // tiles of eight and sixteen waves; 15, 16 the 64 x 64 and 64 x 128 tiles with the K chunks
 // prefetched two ahead (gemm_wide.hip); 17, 18 the streaming persistent form without and
 // with the C tile loaded at the start of a tile's last chunk; 19 tiling 2 with the tiles of
-// a job in bands of eight tile rows (gemm.hip); 20 the 64 x 128 tile (13) in bands of eight
+// a job in bands of eight tile rows (gemm.hip), or the FP16-pair update (gemm_half2.hip) where
+// half2_update says so and its scratch is given; 20 the 64 x 128 tile (13) in bands of eight
 // tile rows (gemm_wide.hip).
 void launch_gemm_f32_any(int variant, const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd, int r_begin,
-                         int c_begin, int c_end, float2* work, hipStream_t s) {
+                         int c_begin, int c_end, float2* work, const Half2Scratch& half2, hipStream_t s) {
   const int base = gemm_f32_variants();
   if (variant < base) {
     launch_gemm_f32(variant, jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s);
     return;
   }
   if (variant == base + 9) {
+    if (half2.p && half2_update(rows, kd)) {
+      launch_gemm_half2(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, half2, s);
+      return;
+    }
     launch_gemm_f32_banded(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s);
     return;
   }

@@ -118,6 +118,7 @@ struct lsms_ctx {
   bool lookahead = false;      // factor the next group's first panel on a side stream
   bool symmetric = false;      // split mode: symmetric form and L D L^T instead of LU
   DevBuf ldlt;                 // scratch of its tall panels
+  DevBuf half2[2];             // operand pairs of the FP16-pair update, one per stream that factors waves
   SideStream side;             // created on first use
   hipStream_t capture = nullptr;  // non-blocking stream the graphs are captured on
   std::map<std::vector<intptr_t>, hipGraphExec_t> graph_cache;
@@ -215,6 +216,23 @@ static int tall_scratch(lsms_ctx* ctx, int njobs, int npad_max, TallScratch* ts,
   if (rc) return rc;
   ts->base = ctx->tall.p;
   return LSMS_OK;
+}
+
+// Scratch of the wide updates of a batch of njobs systems of padded size npad_max on stream s
+// (the pipelined waves' second stream has its own).  Where it cannot be allocated the updates run
+// on the FP32 matrix cores, which need none.
+static Half2Scratch half2_scratch(lsms_ctx* ctx, int njobs, int npad_max, const Tiling& t, hipStream_t s) {
+  Half2Scratch h;
+  const size_t bytes = t.wide == kDefaultF32Wide ? half2_scratch_bytes(njobs, npad_max, t.group) : 0;
+  if (bytes == 0) return h;
+  DevBuf& b = ctx->half2[ctx->pipe && s == ctx->pipe ? 1 : 0];
+  if (ensure_dev(b, bytes, s) != LSMS_OK) {
+    (void)hipGetLastError();
+    if (b.bytes < half2_job_bytes(npad_max - t.group * NB, npad_max - t.group * NB, t.group * NB)) return h;
+  }
+  h.p = b.p;
+  h.bytes = b.bytes;
+  return h;
 }
 
 static int ensure_pinned(lsms_ctx* c, size_t bytes, hipStream_t s) {
@@ -365,6 +383,8 @@ extern "C" int lsms_destroy(lsms_ctx* ctx) {
   if (ctx->fallback_mat.p) hipFree(ctx->fallback_mat.p);
   if (ctx->tall.p) hipFree(ctx->tall.p);
   if (ctx->ldlt.p) hipFree(ctx->ldlt.p);
+  for (DevBuf& b : ctx->half2)
+    if (b.p) hipFree(b.p);
   for (auto& kv : ctx->graph_cache) hipGraphExecDestroy(kv.second);
   if (ctx->capture) hipStreamDestroy(ctx->capture);
   if (ctx->side.update_done) hipEventDestroy(ctx->side.update_done);
@@ -687,6 +707,8 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
     rc = ensure_dev(ctx->ldlt, ldlt_scratch_bytes(nj), s);
     if (rc) return rc;
   }
+  const Half2Scratch half2 =
+      precision == LSMS_SPLIT && !sym ? half2_scratch(ctx, nj, npad_max, tiling, s) : Half2Scratch{};
   const SideStream* side = nullptr;
   const bool capture = ctx->graphs && !prof;
   if (!capture) {  // captured graphs keep the single-stream order
@@ -701,7 +723,7 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
       if (sym)
         ldlt_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, variant, NB, ctx->ldlt.p);
       else
-        lu_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, tiling, ts, side);
+        lu_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, tiling, ts, half2, side);
       // the first solve in FP32 on a rounded copy of the right-hand side (refined below)
       launch_x32(jd, nj, npad_max, 0, xbuf, xbuf, nullptr, q);
       lu_solve_f32_single(jd, nj, npad_max, (const float2*)abuf, piv, xbuf, nullptr, tiling.group, q);
@@ -717,7 +739,8 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
                                      tiling.group,
                                      (intptr_t)jd, (intptr_t)abuf,
                                      (intptr_t)piv, (intptr_t)jinfo, (intptr_t)xbuf, ts.chunk,
-                                     (intptr_t)ts.base, sym ? 1 : 0, (intptr_t)ctx->ldlt.p};
+                                     (intptr_t)ts.base, sym ? 1 : 0, (intptr_t)ctx->ldlt.p,
+                                     (intptr_t)half2.p, (intptr_t)half2.bytes};
   auto it = ctx->graph_cache.find(key);
   if (it == ctx->graph_cache.end()) {
     if (!ctx->capture) HIP_TRY(hipStreamCreateWithFlags(&ctx->capture, hipStreamNonBlocking));
@@ -1567,7 +1590,8 @@ extern "C" int lsms_batched_lu_solve(lsms_ctx* ctx, int32_t batch, const int32_t
     lu_solve_f64(jd, batch, npad_max, (const double2*)abuf, piv, xbuf, 0, 16, 0, tl.group, s);
   } else {
     const Tiling tl = pick_tiling(ctx, prec, npad_max);
-    lu_factor_f32(jd, batch, npad_max, (float2*)abuf, piv, info, s, nullptr, tl, ts);
+    lu_factor_f32(jd, batch, npad_max, (float2*)abuf, piv, info, s, nullptr, tl, ts,
+                  half2_scratch(ctx, batch, npad_max, tl, s));
     lu_solve_f32(jd, batch, npad_max, (const float2*)abuf, piv, xbuf, 0, 16, 0, tl.group, s);
   }
   launch_store_user(jd, batch, npad_max, bptr, nrhs, xbuf, s);

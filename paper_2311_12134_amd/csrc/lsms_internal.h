@@ -187,8 +187,22 @@ int peak_probe(int what, int cu_count, hipStream_t s, double* value);
 int gemm_f32_variants();
 // All FP32 tilings: those of gemm.hip and the persistent forms (gemm_persist.hip).
 int gemm_f32_variants_all();
+// Scratch of the FP16-pair update (gemm_half2.hip): p == nullptr, or at least one job's share.
+struct Half2Scratch {
+  void* p = nullptr;
+  size_t bytes = 0;
+};
+// Whether the default tiling (19) takes the FP16-pair update; one job's share of its scratch.
+bool half2_update(int rows, int kd);
+size_t half2_job_bytes(int rows, int cols, int kd);
+// Scratch for the wide updates of a batch (0: none of them takes the FP16-pair update): every
+// job's share, but no more than HALF2_SCRATCH_MAX or one job's share, whichever is larger.
+constexpr size_t HALF2_SCRATCH_MAX = (size_t)1 << 30;
+size_t half2_scratch_bytes(int njobs, int npad_max, int group);
+void launch_gemm_half2(const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd, int r_begin, int c_begin,
+                       int c_end, float2* work, const Half2Scratch& scratch, hipStream_t s);
 void launch_gemm_f32_any(int variant, const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd, int r_begin,
-                         int c_begin, int c_end, float2* work, hipStream_t s);
+                         int c_begin, int c_end, float2* work, const Half2Scratch& half2, hipStream_t s);
 void launch_gemm_f32(int variant, const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd, int r_begin,
                      int c_begin, int c_end, float2* work, hipStream_t s);
 void launch_gemm_f32_lower(const JobDesc* jobs, int njobs, int rows, int k, int kd, int rc_begin, float2* work,
@@ -216,7 +230,7 @@ void lu_factor_f64(const JobDesc* jobs, int njobs, int npad_max, double2* work, 
                    const SideStream* side = nullptr);
 void lu_factor_f32(const JobDesc* jobs, int njobs, int npad_max, float2* work, int32_t* piv, int32_t* info,
                    hipStream_t s, GemmProfiler* prof, Tiling tiling, const TallScratch& tall,
-                   const SideStream* side = nullptr);
+                   const Half2Scratch& half2, const SideStream* side = nullptr);
 // Symmetric factorization S = L D L^T of complex-symmetric systems (no pivoting), stored as
 // an LU with U = D L^T so the LU solves apply.  Panels taller than tall_rows take the
 // diagonal-block path, which needs ldlt_scratch_bytes(njobs) bytes of device scratch.

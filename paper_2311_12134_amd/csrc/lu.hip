@@ -1494,11 +1494,13 @@ void lu_factor_f64(const JobDesc* jobs, int njobs, int npad_max, double2* work, 
 }
 
 void lu_factor_f32(const JobDesc* jobs, int njobs, int npad_max, float2* work, int32_t* piv, int32_t* info,
-                   hipStream_t s, GemmProfiler* prof, Tiling tiling, const TallScratch& tall, const SideStream* side) {
+                   hipStream_t s, GemmProfiler* prof, Tiling tiling, const TallScratch& tall,
+                   const Half2Scratch& half2, const SideStream* side) {
   lu_factor_any<float2>(jobs, njobs, npad_max, work, piv, info, s, prof, tall, side, tiling.panel_small_rows,
                         tiling.group, [&](int rows, int cols, int k, int kd, int rb, int cb, int ce) {
-                          launch_gemm_f32_any(kd < tiling.group * NB ? tiling.narrow : tiling.wide, jobs, njobs,
-                                              rows, cols, k, kd, rb, cb, ce, work, s);
+                          const bool wide = kd == tiling.group * NB;
+                          launch_gemm_f32_any(wide ? tiling.wide : tiling.narrow, jobs, njobs, rows, cols, k, kd, rb,
+                                              cb, ce, work, wide ? half2 : Half2Scratch{}, s);
                         });
 }
 

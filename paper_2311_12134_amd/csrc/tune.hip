@@ -101,6 +101,11 @@ int update_autotune(int precision, int kind, int npad, int batch, int group, hip
   const int kd = kind == 1 ? group * NB : (group - 1) * NB;
   const int rows = npad - kd, cols = kind == 1 ? rows : NB, c_end = kind == 1 ? 0 : kd + NB;
   const int nv = f64 ? gemm_f64_variants() : gemm_f32_variants_all();
+  Half2Scratch half2;
+  if (!f64 && kind == 1 && half2_update(rows, kd)) {
+    half2.bytes = half2_scratch_bytes(batch, npad, group);
+    if (hipMalloc(&half2.p, half2.bytes) != hipSuccess) return -1;
+  }
   *best = -1;
   for (int v = 0; v < nv; ++v) {
     const float t = tb.time(
@@ -108,14 +113,19 @@ int update_autotune(int precision, int kind, int npad, int batch, int group, hip
           if (f64)
             launch_gemm_f64_variant(v, tb.jd, batch, rows, cols, 0, kd, kd, kd, c_end, (double2*)tb.a, s);
           else
-            launch_gemm_f32_any(v, tb.jd, batch, rows, cols, 0, kd, kd, kd, c_end, (float2*)tb.a, s);
+            launch_gemm_f32_any(v, tb.jd, batch, rows, cols, 0, kd, kd, kd, c_end, (float2*)tb.a, half2, s);
         },
         s);
-    if (t < 0.f) return -1;
+    if (t < 0.f) {
+      *best = -1;
+      break;
+    }
     ms[v] = t;
     if (*best < 0 || t < ms[*best]) *best = v;
   }
-  return hipStreamSynchronize(s) == hipSuccess ? 0 : -1;
+  const bool ok = hipStreamSynchronize(s) == hipSuccess && *best >= 0;
+  hipFree(half2.p);
+  return ok ? 0 : -1;
 }
 
 int panel_autotune(int rows, int batch, hipStream_t s, float* ms) {
