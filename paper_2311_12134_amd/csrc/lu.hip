@@ -25,7 +25,6 @@
 
 #include "lsms_internal.h"
 #include "strip_mma.h"
-#include "tri.h"
 
 namespace lsms {
 
@@ -611,80 +610,46 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
 // inverses of the panel's diagonal triangles, in place
 // ------------------------------------------------------------------------------------
 // After panel(k) the diagonal block holds L11 (strictly lower, unit diagonal implied) and
-// U11 (upper with diagonal).  One workgroup per job solves L11 X = I and U11 Y = I (four
-// wavefronts of 16 columns each per triangle, FP64 shuffle substitution, tri.h) and overwrites the block with
-// X = L11^-1 below the diagonal and Y = U11^-1 on and above it.  Every later use of the
-// block wants an inverse: U12 = L11^-1 A12 in swap_trsm_kernel and the four diagonal steps
-// of the solves, which thereby become products on the matrix cores.  No later interchange
-// touches the block (pivots of later panels lie below it), and nothing else reads U11.
-// This form serves FP64 storage; FP32 storage takes the blocked kernel below.
+// U11 (upper with diagonal).  One workgroup per job overwrites the block with X = L11^-1 below
+// the diagonal and Y = U11^-1 on and above it.  Every later use of the block wants an inverse:
+// U12 = L11^-1 A12 in swap_trsm_kernel and the four diagonal steps of the solves, which
+// thereby become products on the matrix cores.  No later interchange touches the block (pivots
+// of later panels lie below it), and nothing else reads U11.
+//
+// Blocked in 16 x 16 blocks (indices i, m in 0..3): one wavefront per diagonal block forms
+// X_ii = L_ii^-1 or Y_ii = U_ii^-1 (16-step FP64 substitutions), then the off-diagonal blocks
+// follow from FP64 matrix-core products:
+//   X_ij = -sum_{j <= m < i} (X_ii L_im) X_mj,   Y_ij = -sum_{i < m <= j} (Y_ii U_im) Y_mj,
+// first the six products W = X_ii L_im and the six Y_ii U_im, then the blocks one, two and
+// three steps off the diagonal (waves 0-3 the lower triangle, 4-7 the upper one).  Results
+// are kept in FP64 and rounded once to the storage precision at the store.  With FP64 storage W
+// overwrites the blocks of L11 and U11 it is formed from (133 KB of LDS, one workgroup per
+// compute unit).  A chain of about 50 dependent steps bounds it.  FP64 storage on one system:
+// 18 us, against 83 for two 64-step substitutions one after the other.
+__device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl(v.x, src), __shfl(v.y, src)); }
+__device__ inline void lower_pair(int task, int& i, int& m) {  // (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
+  i = 1 + (task >= 1) + (task >= 3);
+  m = task - i * (i - 1) / 2;
+}
 template <typename T>
 __global__ __launch_bounds__(512) void linv_kernel(const JobDesc* jobs, int k, T* work) {
+  constexpr int B = 16;
   const JobDesc jd = jobs[blockIdx.x];
   if (k >= jd.npad) return;  // uniform
   T* A = work + jd.a_off;
   const int64_t ld = jd.npad;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  typedef typename LdsOf<T>::type S;
-  // FP32 storage: both inverses at once (waves 0-3 L11, 4-7 U11, 100 KB of LDS); FP64
-  // storage: one after the other in two arrays (133 KB), waves 4-7 idle
-  constexpr bool BOTH = sizeof(S) == sizeof(float2);
-  __shared__ S s_T[NB][NB + 1];
-  __shared__ S s_X[NB][NB + 1];
-  __shared__ S s_Y[BOTH ? NB : 1][NB + 1];
-  for (int idx = t; idx < NB * NB; idx += 512) {
-    const int q = idx / NB, pp = idx % NB;
-    s_T[q][pp] = A[(k + q) * ld + k + pp];
-    st2(&s_X[q][pp], make_double2(q == pp ? 1.0 : 0.0, 0.0));
-    if (BOTH) st2(&s_Y[BOTH ? q : 0][pp], make_double2(q == pp ? 1.0 : 0.0, 0.0));
-  }
-  __syncthreads();
-  // the substitutions read only the triangle they need (tri.h)
-  if (wave < 4) tri_unit_lower<16>(&s_T[0][0], NB + 1, &s_X[0][0], NB + 1, wave * 16, lane);
-  if (BOTH && wave >= 4) tri_upper<16>(&s_T[0][0], NB + 1, &s_Y[0][0], NB + 1, (wave - 4) * 16, lane);
-  __syncthreads();
-  if (BOTH) {
-    for (int idx = t; idx < NB * NB; idx += 512) {
-      const int q = idx / NB, pp = idx % NB;
-      A[(k + q) * ld + k + pp] = pp < q ? s_X[q][pp] : s_Y[BOTH ? q : 0][pp];
-    }
-    return;
-  }
-  for (int idx = t; idx < NB * NB; idx += 512) {
-    const int q = idx / NB, pp = idx % NB;
-    if (pp < q) A[(k + q) * ld + k + pp] = s_X[q][pp];
-    st2(&s_X[q][pp], make_double2(q == pp ? 1.0 : 0.0, 0.0));
-  }
-  __syncthreads();
-  if (wave < 4) tri_upper<16>(&s_T[0][0], NB + 1, &s_X[0][0], NB + 1, wave * 16, lane);
-  __syncthreads();
-  for (int idx = t; idx < NB * NB; idx += 512) {
-    const int q = idx / NB, pp = idx % NB;
-    if (pp >= q) A[(k + q) * ld + k + pp] = s_X[q][pp];
-  }
-}
-
-// FP32 storage: the same inverses blocked in 16 x 16 blocks (indices i, m in 0..3).  One
-// wavefront per diagonal block forms X_ii = L_ii^-1 or Y_ii = U_ii^-1 (16-step FP64
-// substitutions), then the off-diagonal blocks follow from FP64 matrix-core products:
-//   X_ij = -sum_{j <= m < i} (X_ii L_im) X_mj,   Y_ij = -sum_{i < m <= j} (Y_ii U_im) Y_mj,
-// first the six products W = X_ii L_im and the six Y_ii U_im, then the blocks one, two and
-// three steps off the diagonal (waves 0-3 the lower triangle, 4-7 the upper one).  Results
-// are kept in FP64 and rounded once to FP32 at the store.
-__device__ inline void lower_pair(int task, int& i, int& m) {  // (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
-  i = 1 + (task >= 1) + (task >= 3);
-  m = task - i * (i - 1) / 2;
-}
-__global__ __launch_bounds__(512) void linv_blocked_kernel(const JobDesc* jobs, int k, float2* work) {
-  constexpr int B = 16;
-  const JobDesc jd = jobs[blockIdx.x];
-  if (k >= jd.npad) return;  // uniform
-  float2* A = work + jd.a_off;
-  const int64_t ld = jd.npad;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  __shared__ float2 s_T[NB][NB + 1];           // L11 \ U11 as factored
+  constexpr bool IN_PLACE = sizeof(T) == sizeof(double2);
+  __shared__ T s_T[NB][NB + 1];                // L11 \ U11 as factored
   __shared__ double2 s_V[NB][NB + 1];          // X = L11^-1 below the diagonal, Y = U11^-1 on and above
-  __shared__ double2 s_W[2][6][B][B + 1];      // X_ii L_im (index i (i - 1) / 2 + m) and Y_mm U_mi
+  __shared__ double2 s_W[2][IN_PLACE ? 1 : 6][B][B + 1];  // X_ii L_im (index i (i - 1) / 2 + m) and Y_mm U_mi
+  // entry (r, c) of W_im (lower, i > m) or of Y_mm U_mi (upper)
+  auto w_at = [&](bool low, int i, int m, int r, int c) -> double2& {
+    if constexpr (IN_PLACE)
+      return low ? s_T[i * B + r][m * B + c] : s_T[m * B + r][i * B + c];
+    else
+      return s_W[low ? 0 : 1][i * (i - 1) / 2 + m][r][c];
+  };
   for (int idx = t; idx < NB * NB; idx += 512) {
     const int q = idx / NB, pp = idx % NB;
     s_T[q][pp] = A[(k + q) * ld + k + pp];
@@ -748,7 +713,7 @@ __global__ __launch_bounds__(512) void linv_blocked_kernel(const JobDesc* jobs, 
       acc.run([&](int r, int kk) { return diag_at(m, r, kk); },
               [&](int kk, int cc) { return ld2(&s_T[m * B + kk][i * B + cc]); }, lane);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s_W[lower ? 0 : 1][task][Mma::row(r, lane)][c] = acc.value(0, r);
+    for (int r = 0; r < 4; ++r) w_at(lower, i, m, Mma::row(r, lane), c) = acc.value(0, r);
   }
   __syncthreads();
   // blocks dd steps off the diagonal: lower X_{i, i-dd}, upper Y_{i-dd, i}, i = dd .. 3
@@ -761,11 +726,11 @@ __global__ __launch_bounds__(512) void linv_blocked_kernel(const JobDesc* jobs, 
       acc.zero();
       for (int m = j; m < i; ++m) {  // lower: W_im X_mj; upper: (Y_jj U_jm... ) as W(j, m) Y_mi
         if (lower)
-          acc.run([&](int r, int kk) { return s_W[0][i * (i - 1) / 2 + m][r][kk]; },
+          acc.run([&](int r, int kk) { return w_at(true, i, m, r, kk); },
                   [&](int kk, int cc) { return m == j ? diag_at(j, kk, cc) : s_V[m * B + kk][j * B + cc]; }, lane);
         else {
           const int mm = m + 1;  // Y_{j, i} = -sum_{j < mm <= i} (Y_jj U_{j mm}) Y_{mm, i}
-          acc.run([&](int r, int kk) { return s_W[1][mm * (mm - 1) / 2 + j][r][kk]; },
+          acc.run([&](int r, int kk) { return w_at(false, mm, j, r, kk); },
                   [&](int kk, int cc) { return mm == i ? diag_at(i, kk, cc) : s_V[mm * B + kk][i * B + cc]; }, lane);
         }
       }
@@ -789,10 +754,7 @@ __global__ __launch_bounds__(512) void linv_blocked_kernel(const JobDesc* jobs, 
 
 template <typename T>
 static void launch_linv(const JobDesc* jobs, int njobs, int k, T* work, hipStream_t s) {
-  if constexpr (sizeof(T) == sizeof(float2))
-    linv_blocked_kernel<<<njobs, 512, 0, s>>>(jobs, k, work);
-  else
-    linv_kernel<T><<<njobs, 512, 0, s>>>(jobs, k, work);
+  linv_kernel<T><<<njobs, 512, 0, s>>>(jobs, k, work);
 }
 
 // ------------------------------------------------------------------------------------
