@@ -386,8 +386,8 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * tilings of the narrow (a panel's 64 columns within its group, K < 64 x group) and wide
  * (K = 64 x group) trailing updates.
  * knob LSMS_TUNE_PANEL_SMALL_ROWS (0 .. 768, default 768): split-mode panels of at most this
- * many rows run in 256-thread workgroups with 8-wide leaves (three jobs per compute unit),
- * taller ones in 512-thread workgroups with 16-wide leaves (one job per compute unit).
+ * many rows run in 256-thread workgroups (two jobs per compute unit), taller ones in
+ * 512-thread workgroups (one job per compute unit).
  * For every such choice (and LSMS_TUNE_GEMM_F32), -1 (the initial value) means: the
  * autotuned choice for the wave's padded size (lsms_autotune_kernel), else the library
  * default.  lsms_get_tuning reports the explicit setting (-1 if none), except for
@@ -420,7 +420,7 @@ int lsms_get_tuning(lsms_ctx* ctx, int knob, int* value);
  *   LSMS_AUTOTUNE_F32_PANEL: the two split-mode panel variants at the LSMS_PANEL_HEIGHTS
  *     heights 256, 512 and 768 (npad ignored; batch systems of the
  *     panel's 64 columns); ms[2 h + v] (ms_len >= 2 LSMS_PANEL_HEIGHTS) receives variant v
- *     (0: 256 threads, 8-wide leaves; 1: 512 threads) at height h, and the context's panel
+ *     (0: 256 threads; 1: 512 threads) at height h, and the context's panel
  *     threshold becomes the height T (0: none) for which the small variant up to T and the
  *     large one above give the least summed time over the measured heights; *best receives T.
  * For the updates the fastest tiling (the library default unless another is faster by more

@@ -8,8 +8,8 @@
 //                     partial pivoting (pivot = largest |re|+|im|, first on ties, keys
 //                     compared in FP64): IB-wide leaves live in registers (rows distributed
 //                     cyclically over the workgroup) and are updated in the storage
-//                     precision, every pivot swaps the whole panel row, and the rest of the
-//                     panel is updated by the leaf (triangular solve + rank-IB).
+//                     precision, a leaf's interchanges then move whole panel rows, and the rest
+//                     of the panel is updated by the leaf (triangular solve + rank-IB).
 //   swap_trsm_kernel  applies the panel's row interchanges to the trailing columns and
 //                     forms U12 = L11^-1 A12 (one workgroup per 64-column tile).
 //   gemm_*_kernel     (gemm.hip) trailing update A22 -= L21 U12 on the matrix cores:
@@ -22,6 +22,7 @@
 // Matrices are row-major with leading dimension npad (a multiple of 64); the padding
 // is an identity block that no pivot ever selects.
 #include <algorithm>
+#include <type_traits>
 
 #include "lsms_internal.h"
 #include "strip_mma.h"
@@ -34,48 +35,77 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // panel factorization
 // ------------------------------------------------------------------------------------
 // Pivot keys: a non-negative double orders like its bit pattern, so the magnitude with
-// its 13 lowest mantissa bits replaced by (8191 - local row) is one 64-bit integer whose
-// maximum is the largest magnitude, the lowest row on ties (relative resolution 2^-39).
+// its 13 lowest mantissa bits replaced by (8191 - position) is one 64-bit integer whose
+// maximum is the largest magnitude, the lowest position on ties (relative resolution 2^-39).
 // NaN magnitudes get key 0 and never win; key 0 overall means "keep the diagonal row".
-__device__ inline unsigned long long pivot_key(double mag, int row_local) {
-  if (!(mag == mag)) return 0ull;
-  return ((unsigned long long)__double_as_longlong(mag) & ~0x1FFFull) | (unsigned long long)(0x1FFF - row_local);
+struct PivotKey {
+  unsigned hi, lo;
+};
+__device__ inline PivotKey pivot_key(double mag, int pos) {
+  if (!(mag == mag)) return PivotKey{0u, 0u};
+  const unsigned long long b = (unsigned long long)__double_as_longlong(mag);
+  return PivotKey{(unsigned)(b >> 32), ((unsigned)b & ~0x1FFFu) | (unsigned)(0x1FFF - pos)};
 }
-__device__ inline int pivot_row(unsigned long long key) { return 0x1FFF - (int)(key & 0x1FFFull); }
+__device__ inline bool key_less(PivotKey a, PivotKey b) { return a.hi < b.hi || (a.hi == b.hi && a.lo < b.lo); }
+__device__ inline int pivot_pos(unsigned lo) { return 0x1FFF - (int)(lo & 0x1FFFu); }
 
-// One lane's 64-bit key moved within its 16-lane row by the DPP pattern CTRL.
+// One lane's value moved within its 16-lane row by the DPP pattern CTRL.
 template <int CTRL>
-__device__ inline unsigned long long dpp_key(unsigned long long x) {
-  const int lo = (int)(unsigned)x, hi = (int)(unsigned)(x >> 32);
-  const unsigned rlo = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
-  const unsigned rhi = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false);
-  return ((unsigned long long)rhi << 32) | rlo;
+__device__ inline unsigned dpp_u32(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xF, 0xF, false);
 }
-__device__ inline unsigned long long umax64(unsigned long long a, unsigned long long b) { return a > b ? a : b; }
-__device__ inline unsigned long long lane_key(unsigned long long x, int l) {
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), l);
-  return ((unsigned long long)hi << 32) | lo;
+__device__ inline unsigned lane_u32(unsigned x, int l) { return (unsigned)__builtin_amdgcn_readlane((int)x, l); }
+// Largest value of lanes 0 .. N - 1 (N <= 16: the other lanes of the row hold 0; 64: the wavefront), a
+// scalar: the maximum within each 16-lane row by DPP (quad exchanges 1 and 2, half-row mirror, row
+// mirror; each step combines groups that already agree), then the four rows' maxima.
+template <int N>
+__device__ inline unsigned lanes_max(unsigned x) {
+  x = max(x, dpp_u32<0xB1>(x));              // quad_perm [1, 0, 3, 2]
+  if (N > 2) x = max(x, dpp_u32<0x4E>(x));   // quad_perm [2, 3, 0, 1]
+  if (N > 4) x = max(x, dpp_u32<0x141>(x));  // row_half_mirror
+  if (N > 8) x = max(x, dpp_u32<0x140>(x));  // row_mirror
+  if (N <= 16) return lane_u32(x, 0);
+  return max(max(lane_u32(x, 0), lane_u32(x, 16)), max(lane_u32(x, 32), lane_u32(x, 48)));
 }
-// Largest key of the wavefront, the same in every lane: the maximum within each 16-lane
-// row by DPP (quad exchanges 1 and 2, half-row mirror, row mirror; each step combines
-// groups that already agree), then the four rows' maxima read as scalars.
-__device__ inline unsigned long long wave_max_key(unsigned long long key) {
-  key = umax64(key, dpp_key<0xB1>(key));   // quad_perm [1, 0, 3, 2]
-  key = umax64(key, dpp_key<0x4E>(key));   // quad_perm [2, 3, 0, 1]
-  key = umax64(key, dpp_key<0x141>(key));  // row_half_mirror
-  key = umax64(key, dpp_key<0x140>(key));  // row_mirror
-  return umax64(umax64(lane_key(key, 0), lane_key(key, 16)), umax64(lane_key(key, 32), lane_key(key, 48)));
+// The lane (of lanes 0 .. N - 1) with the largest key, the same in every lane; hi is the largest high
+// word, and the low words count only where it ties.
+template <int N>
+__device__ inline int best_lane(PivotKey key, unsigned hi) {
+  unsigned long long m = __ballot(key.hi == hi);
+  if (m & (m - 1)) {  // uniform
+    const unsigned lo = lanes_max<N>(key.hi == hi ? key.lo : 0u);
+    m = __ballot(key.hi == hi && key.lo == lo);
+  }
+  return __ffsll((long long)m) - 1;
 }
 
-// Inverse of a pivot in FP64.  Values stored in FP32 have squared magnitudes well inside
-// the FP64 range, so conj(a) / |a|^2 needs one division; FP64 storage keeps the scaled
-// (Smith) form.
+__device__ inline float2 lane_value(float2 x, int l) {
+  return make_float2(__uint_as_float(lane_u32(__float_as_uint(x.x), l)), __uint_as_float(lane_u32(__float_as_uint(x.y), l)));
+}
+__device__ inline double2 lane_value(double2 x, int l) {
+  return make_double2(__hiloint2double(lane_u32(__double2hiint(x.x), l), lane_u32(__double2loint(x.x), l)),
+                      __hiloint2double(lane_u32(__double2hiint(x.y), l), lane_u32(__double2loint(x.y), l)));
+}
+
+// Inverse of a pivot in FP64, conj(a) / |a|^2.  Values stored in FP32 have squared magnitudes well
+// inside the FP64 range; FP64 values are first scaled by a power of two that brings the larger
+// component to [1/2, 1).  1 / |a|^2 by two Newton steps on the hardware's reciprocal (24 bits or
+// more, so the second step ends at FP64's own rounding), a third of the chain of a division.
+__device__ inline double recip(double n) {
+  double r = __builtin_amdgcn_rcp(n);
+  r = __builtin_fma(__builtin_fma(-n, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-n, r, 1.0), r, r);
+}
 __device__ inline double2 pivot_inverse(double2 a, float2) {
-  const double rn = 1.0 / (a.x * a.x + a.y * a.y);
+  const double rn = recip(__builtin_fma(a.x, a.x, a.y * a.y));
   return make_double2(a.x * rn, -a.y * rn);
 }
-__device__ inline double2 pivot_inverse(double2 a, double2) { return cinv(a); }
+__device__ inline double2 pivot_inverse(double2 a, double2) {
+  const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(a.x), fabs(a.y)));
+  const double x = __builtin_amdgcn_ldexp(a.x, e), y = __builtin_amdgcn_ldexp(a.y, e);
+  const double rn = recip(__builtin_fma(x, x, y * y));
+  return make_double2(__builtin_amdgcn_ldexp(x * rn, e), __builtin_amdgcn_ldexp(-y * rn, e));
+}
 
 // a - b c for the leaf's rank-1 updates: each component as two fused multiply-adds (two
 // roundings, where the product-then-difference form takes three operations and three roundings)
@@ -93,31 +123,21 @@ __device__ inline double2 wide(float2 a) { return make_double2((double)a.x, (dou
 __device__ inline void narrow_to(double2& d, double2 a) { d = a; }
 __device__ inline void narrow_to(float2& d, double2 a) { d = make_float2((float)a.x, (float)a.y); }
 
-// IB consecutive elements of one row, moved 16 bytes at a time (rows start 16-byte aligned)
-template <int IB>
-__device__ inline void load_row(const float2* p, float2 (&d)[IB]) {
-#pragma unroll
-  for (int u = 0; u < IB / 2; ++u) {
-    const float4 x = ((const float4*)p)[u];
-    d[2 * u] = make_float2(x.x, x.y);
-    d[2 * u + 1] = make_float2(x.z, x.w);
-  }
+// c ? a : b by components (a choice between two array elements as a whole would be a choice of their
+// addresses, and put the arrays in memory)
+__device__ inline float2 sel(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
+__device__ inline double2 sel(bool c, double2 a, double2 b) { return make_double2(c ? a.x : b.x, c ? a.y : b.y); }
+// a 16-byte piece of a staged row, to and from LDS (FP32 rows are only 8-byte aligned there)
+__device__ inline void chunk_put(float2* d, float4 x) {
+  d[0] = make_float2(x.x, x.y);
+  d[1] = make_float2(x.z, x.w);
 }
-template <int IB>
-__device__ inline void load_row(const double2* p, double2 (&d)[IB]) {
-#pragma unroll
-  for (int u = 0; u < IB; ++u) d[u] = p[u];
+__device__ inline void chunk_put(double2* d, float4 x) { *(float4*)d = x; }
+__device__ inline float4 chunk_get(const float2* d) {
+  const float2 a = d[0], b = d[1];
+  return make_float4(a.x, a.y, b.x, b.y);
 }
-template <int IB>
-__device__ inline void store_row(float2* p, const float2 (&d)[IB]) {
-#pragma unroll
-  for (int u = 0; u < IB / 2; ++u) ((float4*)p)[u] = make_float4(d[2 * u].x, d[2 * u].y, d[2 * u + 1].x, d[2 * u + 1].y);
-}
-template <int IB>
-__device__ inline void store_row(double2* p, const double2 (&d)[IB]) {
-#pragma unroll
-  for (int u = 0; u < IB; ++u) p[u] = d[u];
-}
+__device__ inline float4 chunk_get(const double2* d) { return *(const float4*)d; }
 // Orders LDS traffic between the lanes of one wavefront (its LDS operations run in order).
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -125,6 +145,14 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl(v.x, src), __shfl(v.y, src)); }
+// A barrier that orders LDS only: the pivot columns' data passes through LDS, and waiting for a
+// leaf's stores to memory there would lengthen their chain.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 // The NB interchanges of a panel starting at row k (pivall[q]: the row exchanged with
 // k + q at step q) as one permutation of at most 2 NB rows, written to lst: entries
 // 0..NB-1 are the positions k..k+NB-1, further entries the pivot rows below the panel;
@@ -171,319 +199,314 @@ __device__ inline int write_perm_list(int k, const int* pivall, int* s_pos, int*
 
 // nopiv: keep the diagonal row at every step (the symmetric factorization below); the
 // permutation list is then the identity.
+//
+// One workgroup per job; thread t holds rows t, t + PT, .. of the panel (S of them), one leaf of IB
+// columns at a time, in registers.  Rows stay with their threads while a leaf is factored: an
+// interchange only exchanges two numbers, the positions pos[] of the rows, and the leaf is stored at
+// its rows' positions at the end, from which the list of the rows that moved follows in parallel.
+// A pivot column has two barriers: before the first every wavefront posts its best key and that
+// pivot's inverse (formed by every lane for its own best row while the keys are reduced, so it is
+// off the chain); then the winner alone posts its row (a row posted by every wavefront, one lane's
+// 16-byte stores at a time, fills the LDS pipe: 150 000 cycles for the 64 columns of 256 FP32
+// rows, 137 000 this way), and every wavefront reads it once, entry q in lane q.
+// Bound by that chain, about 2200 cycles a column, by the update's arithmetic from three row
+// slots on, and for tall panels by the rank-IB updates' traffic.  Leaves are as wide as the
+// registers allow, since every leaf pays once for loading, storing, interchanging the other columns
+// and the rank update.  One panel, on 2 and on 320 systems (us; before: rows exchanged in
+// registers, the moved rows listed by one thread, leaves of 8 and 16): FP64 256 rows 112 / 180
+// (173 / 356), 320 rows 153 / 333 (195 / 402), 768 rows 195 / 499 (283 / 690), 2048 rows 430 / 1437
+// (515 / 1633); FP32 256 rows 88 (147), 512 rows 118 / 176 (199 / 282), 1024 rows 160 / 380 (211 / 469),
+// 2048 rows 250 / 635 (283 / 689), 2176 rows 320 / 936 (354 / 929).
 template <typename T, int PT, int S, int IB>
-__global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, int left, T* work, int32_t* piv,
+__global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k, int left, T* work, int32_t* piv,
                                                    int32_t* info, int nopiv) {
   const JobDesc jd = jobs[blockIdx.x];
   if (k >= jd.npad) return;  // uniform over the workgroup
-  T* A = work + jd.a_off;
-  const int64_t ld = jd.ld > 0 ? jd.ld : jd.npad;
-  const int nrows = jd.npad;
+  const int ld = jd.ld > 0 ? jd.ld : jd.npad;
+  // row r, column c of the matrix, r from the panel's first row: 32-bit byte offsets (a panel of at most
+  // 4096 rows of at most 16384 columns spans 1 GiB).  Each section takes the leading dimension
+  // through here(), which keeps its addresses from being formed ahead and held across the leaves.
+  char* const A = (char*)(work + jd.a_off + (int64_t)k * ld);
+  auto at = [A](int r, int c, int ldx) -> T* { return (T*)(A + (unsigned)(r * ldx + c) * (unsigned)sizeof(T)); };
+  auto here = [ld]() {
+    int x = ld;
+    asm volatile("" : "+s"(x));
+    return x;
+  };
+  const int nrows = jd.npad - k;             // rows, positions and pivots below are relative to k
   int32_t* ip = piv + jd.piv_off;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   constexpr int NW = PT / 64;
+  constexpr int SEG = IB * (int)sizeof(T) < 128 ? IB : 128 / (int)sizeof(T);  // columns moved per staged access
+  constexpr int CPR = SEG * (int)sizeof(T) / 16, RPI = 64 / CPR;  // 16-byte chunks per row, rows per access
+  constexpr int PER = 16 / (int)sizeof(T);                        // elements per chunk
+  constexpr bool ONE = IB == NB;                                  // the whole panel is one leaf
+  constexpr int BB = IB >= 32 ? 8 : 4;                            // columns per block of the leaf
+  static_assert(IB / BB <= 4 && BB % 2 == 0, "the blocks below; buffers alternate across blocks");
+  // the leaf's register that holds column j once it is factored
+  auto reg_of = [](int j) { return IB - (j / BB + 1) * BB + j % BB; };
 
-  // Per pivot column one barrier: before it every wave posts its best key (LDS atomic
-  // max into one of three rotating slots) and its candidate row, and the owner of the
-  // diagonal row posts that row (two rotating buffers); after it every thread knows the
-  // pivot row and both rows to exchange.  Column j clears slot (j + 1) % 3: its last
-  // readers (column j - 2) passed barrier j - 1 before anyone reaches column j, and its
-  // next writers (column j + 1) start after barrier j.  A row buffer written before
-  // barrier j is rewritten only before barrier j + 2, after every read of column j.
-  __shared__ unsigned long long s_key[3];
-  __shared__ T s_cand[2][NW][IB];
-  __shared__ T s_drow[2][IB];
-  __shared__ int s_piv[IB];
-  __shared__ double2 s_L11[IB][IB];
-  __shared__ double2 s_U[IB][NB];
+  __shared__ PivotKey s_key[NW];
+  __shared__ T s_inv[NW];
+  __shared__ __align__(16) T s_prow[IB];
   __shared__ int s_pivall[NB];
-  __shared__ int s_pos[PERM_MAX], s_org[PERM_MAX];
+  __shared__ T s_L11[ONE ? 1 : IB][IB + 1];
+  __shared__ T s_U[ONE ? 1 : IB][ONE ? 1 : NB - IB];
+  __shared__ unsigned short s_org[ONE ? 1 : S * PT];  // original row at each position, over all leaves
   __shared__ int s_lpos[2 * IB], s_lorg[2 * IB], s_lcnt;
-  __shared__ T s_held[2 * IB][2 * NB - IB];
-  // The next leaf stays on chip for 16-wide FP32 leaves of at most half of the registers and
-  // for the 256-thread kernels' 8-wide FP32 leaves of one or two row slots (the other shapes
-  // run out of registers or occupancy with it).
-  constexpr bool KEEP_NEXT = sizeof(T) == sizeof(float2) && (IB == 16 || (PT == 256 && S <= 2)) && S * IB * 2 <= 128;
-  // FP32 leaves move between memory and the row-per-thread registers through the wave's own
-  // rows of s_X: a row of IB FP32 complex values is IB / 2 16-byte chunks, so a wavefront's
-  // 16-byte access covers 64 / (IB / 2) whole rows (full 128- or 64-byte lines) instead of one
-  // chunk of 64 different rows, which costs one L2 request per lane and is the slow part of
-  // storing a leaf.  The same rows carry the next leaf out of the rank update.
-  constexpr bool STAGE = sizeof(T) == sizeof(float2);
-  constexpr int CPR = IB / 2, RPI = 64 / CPR;  // chunks per leaf row, rows per staged access
-  __shared__ T s_X[STAGE ? PT : 1][IB + 1];  // one row per thread (wave-private rows)
+  __shared__ int s_row[PT];
+  // The next leaf stays on chip for 16-wide FP32 leaves of three or four row slots (the other
+  // shapes run out of registers or occupancy with it).
+  constexpr bool KEEP_NEXT = sizeof(T) == sizeof(float2) && IB == 16 && S * IB * 2 <= 128;
+  // A row of the leaf is moved in pieces of 128 bytes through the wave's own rows of s_X: a
+  // wavefront's 16-byte access then covers eight whole pieces instead of one chunk of 64 different
+  // rows, which costs one L2 request per lane.  The same rows carry the next leaf out of the
+  // rank update.
+  __shared__ __align__(16) T s_X[PT][SEG + 1];  // one row per thread (wave-private rows)
 
-  // the leaf in registers in the storage precision (its updates too; pivot keys in FP64)
   T v[S][IB];
+  int pos[S];
   int first_zero = 0;
-  if (t < 3) s_key[t] = 0ull;
-  __syncthreads();
-  int col = 0;  // pivot columns done so far (selects the rotating slots)
+  if constexpr (!ONE) {
+    for (int i = t; i < S * PT; i += PT) s_org[i] = (unsigned short)i;
+  }
 
+  const int ch = lane % CPR, rsub = lane / CPR;
   for (int c = 0; c < NB / IB; ++c) {
-    const int cl = k + c * IB;
+    const int cl = c * IB;       // the leaf's first row and column
+    const int w = NB - cl - IB;  // panel columns right of the leaf
+    if (t == 0) s_lcnt = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) pos[s] = t + s * PT < nrows ? t + s * PT : -1;
+    int ldx = here();
     if (c == 0 || !KEEP_NEXT) {  // otherwise the leaf came from the previous leaf's rank update
-      if constexpr (STAGE) {
-        const int ch = lane % CPR, rsub = lane / CPR;
-        int kb = k;
-        asm volatile("" : "+s"(kb));  // row addresses are formed here, not held across the leaves
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const int rw = kb + s * PT + wave * 64;  // the wave's first row in this slot
-          if (rw >= nrows) {                      // uniform per wave
+      for (int s = 0; s < S; ++s) {
+        const int rw = s * PT + wave * 64;  // the wave's first row in this slot
+        if (rw >= nrows) {                  // uniform per wave
 #pragma unroll
-            for (int q = 0; q < IB; ++q) v[s][q] = T{0, 0};
-            continue;
-          }
-          float4 x[CPR];
+          for (int q = 0; q < IB; ++q) v[s][q] = T{0, 0};
+          continue;
+        }
+        float4 x[IB / SEG][CPR];
+#pragma unroll
+        for (int g = 0; g < IB / SEG; ++g)
 #pragma unroll
           for (int u = 0; u < CPR; ++u) {
             const int r = rw + u * RPI + rsub;
-            x[u] = (r >= cl && r < nrows) ? *(const float4*)(A + r * ld + cl + 2 * ch) : make_float4(0.f, 0.f, 0.f, 0.f);
+            x[g][u] = (r >= cl && r < nrows) ? *(const float4*)at(r, k + cl + g * SEG + PER * ch, ldx)
+                                             : make_float4(0.f, 0.f, 0.f, 0.f);
           }
 #pragma unroll
-          for (int u = 0; u < CPR; ++u) {
-            T* d = s_X[wave * 64 + u * RPI + rsub] + 2 * ch;
-            d[0] = T{x[u].x, x[u].y};
-            d[1] = T{x[u].z, x[u].w};
-          }
+        for (int g = 0; g < IB / SEG; ++g) {
+#pragma unroll
+          for (int u = 0; u < CPR; ++u) chunk_put(s_X[wave * 64 + u * RPI + rsub] + PER * ch, x[g][u]);
           wave_sync();
 #pragma unroll
-          for (int q = 0; q < IB; ++q) v[s][q] = s_X[t][q];
-          wave_sync();  // every lane has its row before the next slot rewrites them
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const int r = k + t + s * PT;
-          if (r >= cl && r < nrows) {
-            load_row<IB>(A + r * ld + cl, v[s]);
-          } else {
-#pragma unroll
-            for (int q = 0; q < IB; ++q) v[s][q] = T{0, 0};
-          }
+          for (int q = 0; q < SEG; ++q) v[s][g * SEG + q] = s_X[t][q];
+          wave_sync();  // every lane has its row before the next piece rewrites them
         }
       }
     }
-#pragma clang loop unroll(full)
-    for (int j = 0; j < IB; ++j, ++col) {
-      const int d = cl + j;
-      const int buf = col & 1;
-      unsigned long long key = 0ull;
+    // The columns in blocks of BB.  A block's columns run through one rolled loop: registers
+    // 0 .. W - 1 hold the W columns from the block on, the current one in register 0; each step
+    // shifts them down by one as it updates them and puts the finished column last.  The pivot row
+    // takes zeros in the places of the block's finished columns, which keeps those as they are.
+    // After the leaf, register reg_of(j) holds column j.
+    // A column's search (its keys, the wave's best, the pivot's inverse) starts when the step before
+    // has updated that column, and runs beside the rest of that step's update.
+    PivotKey key;
+    T inv;
+    unsigned whi;
+    auto search = [&](int d) {
+      key = PivotKey{0u, 0u};
+      T e = v[0][0];  // the lane's best row's entry
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        const int r = k + t + s * PT;
-        if (!nopiv && r >= d && r < nrows) {
-          const double2 e = wide(v[s][j]);
-          const unsigned long long kk = pivot_key(fabs(e.x) + fabs(e.y), r - k);
-          key = kk > key ? kk : key;
+        const double2 x = wide(v[s][0]);
+        PivotKey kk = pivot_key(nopiv ? 1.0 : fabs(x.x) + fabs(x.y), pos[s]);
+        const bool in = nopiv ? pos[s] == d : pos[s] >= d;
+        kk.hi = in ? kk.hi : 0u;
+        kk.lo = in ? kk.lo : 0u;
+        const bool more = s == 0 || key_less(key, kk);
+        key.hi = more ? kk.hi : key.hi;
+        key.lo = more ? kk.lo : key.lo;
+        if (s > 0) e = sel(more, v[s][0], e);
+      }
+      const double2 x = wide(e);
+      // the pivot's inverse in FP64, rounded once to the storage precision
+      narrow_to(inv, sel(x.x == 0.0 && x.y == 0.0, make_double2(0.0, 0.0), pivot_inverse(x, T{})));
+      whi = lanes_max<64>(key.hi);
+    };
+    search(cl);
+    auto block = [&](auto jb_tag) {
+      constexpr int JB = decltype(jb_tag)::value, W = IB - JB * BB;
+#pragma clang loop unroll(disable)
+      for (int jj = 0; jj < BB; ++jj) {
+        const int d = cl + JB * BB + jj;
+        const int post = best_lane<64>(key, whi);
+        if (lane == post) {  // (a wave without eligible rows posts key 0)
+          s_inv[wave] = inv;
+          s_key[wave] = key;
         }
-      }
-      key = wave_max_key(key);
-      if (key != 0ull) {  // the lane holding the wave's best row posts it (never with nopiv)
-        const int rl = pivot_row(key);
-        if (rl % PT == t) {
-#pragma unroll
-          for (int s = 0; s < S; ++s)
-            if (s == rl / PT) {
-#pragma unroll
-              for (int q = 0; q < IB; ++q) s_cand[buf][wave][q] = v[s][q];
-            }
+        lds_barrier();
+        PivotKey kw{0u, 0u};
+        T iw{};
+        if (lane < NW) {
+          kw = s_key[lane];
+          iw = s_inv[lane];
         }
-      }
-      if (lane == 0) atomicMax(&s_key[col % 3], key);
-      const int od = (d - k) % PT, sd = (d - k) / PT;
-      if (t == od) {
+        const int from = best_lane<NW>(kw, lanes_max<NW>(kw.hi));
+        const unsigned bhi = lane_u32(kw.hi, from), blo = lane_u32(kw.lo, from);
+        T il = lane_value(iw, from);
+        int p = pivot_pos(blo);
+        if ((bhi | blo) == 0u) {  // no row has a comparable magnitude (all NaN): the diagonal row (uniform)
+          p = d;
+          il = T{(decltype(il.x))NAN, (decltype(il.x))NAN};
+        }
 #pragma unroll
         for (int s = 0; s < S; ++s)
-          if (s == sd) {
+          if (pos[s] == p) {
 #pragma unroll
-            for (int q = 0; q < IB; ++q) s_drow[buf][q] = v[s][q];
+            for (int q = 0; q < W; ++q) s_prow[q] = v[s][q];
           }
-      }
-      if (t == 0) s_key[(col + 1) % 3] = 0ull;
-      __syncthreads();
-      // every lane reads the same key: taking it as a scalar makes the pivot row, its slot and
-      // the row buffers uniform, so the interchange below branches per wavefront
-      const unsigned long long bk = s_key[col % 3];
-      const unsigned long long best =
-          ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(bk >> 32)) << 32) |
-          (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)bk);
-      int p = best != 0ull ? k + pivot_row(best) : d;
-      const bool from_cand = best != 0ull && p >= d && p < nrows;
-      if (!from_cand) p = d;
-      const T* prow = from_cand ? s_cand[buf][((p - k) % PT) / 64] : s_drow[buf];
-      const int op = (p - k) % PT, sp = (p - k) / PT;
-      if (t == 0) {
-        s_piv[j] = p;
-        s_pivall[c * IB + j] = p;
-        ip[d] = p;
-      }
-      if (t == od) {
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-          if (s == sd) {
-#pragma unroll
-            for (int q = 0; q < IB; ++q) v[s][q] = prow[q];
-          }
-      }
-      if (t == op && p != d) {
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-          if (s == sp) {
-#pragma unroll
-            for (int q = 0; q < IB; ++q) v[s][q] = s_drow[buf][q];
-          }
-      }
-      const double2 pv = wide(prow[j]);
-      const bool zero = (pv.x == 0.0 && pv.y == 0.0);
-      if (zero && first_zero == 0) first_zero = d + 1;
-      T inv;  // the pivot's inverse in FP64, rounded once to the storage precision
-      narrow_to(inv, zero ? make_double2(0.0, 0.0) : pivot_inverse(pv, T{}));
-      // the leaf's rank-1 update in the storage precision (FP32 in split mode, like the
-      // trailing updates; the pivot keys above compare these values in FP64).  While the
-      // leaf takes at most half of the registers, rows on or above the pivot take a zero
-      // multiplier (which leaves them as they are) so the update has no branches, and each
-      // pivot-row entry is read from LDS once for all S row slots; wider leaves (and eight
-      // row slots) update the slots one by one under a branch, which keeps fewer values live.
-      if constexpr (S * IB * (int)sizeof(T) / 4 <= 128 && S < 8) {
-        T l[S];
+        if (t == 0) s_pivall[d] = p;
+        lds_barrier();
+        // the pivot row, entry q in lane q
+        const T row = sel(lane + jj < W, s_prow[min(lane, W - 1)], T{0, 0});
+        if (bhi == 0u && blo < 0x2000u) {  // perhaps an exact zero (uniform)
+          const T pv = lane_value(row, 0);
+          if (pv.x == 0 && pv.y == 0 && first_zero == 0) first_zero = k + d + 1;
+        }
+        // the interchange, and the leaf's rank-1 update in the storage precision (FP32 in split mode,
+        // like the trailing updates; the pivot keys above compare these values in FP64).  Rows on
+        // or above the pivot take a zero multiplier, which leaves them as they are.
+        T l[S], last[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-          const int r = k + t + s * PT;
-          const bool below = r > d && r < nrows;
-          l[s] = below ? cmul(v[s][j], inv) : T{0, 0};
-          if (below) v[s][j] = l[s];
+          pos[s] = pos[s] == p ? d : pos[s] == d ? p : pos[s];
+          const bool below = pos[s] > d;
+          const T m = cmul(v[s][0], il);
+          l[s] = sel(below, m, T{0, 0});
+          last[s] = sel(below, m, v[s][0]);
         }
+        auto update = [&](int q) {
+          const T u = lane_value(row, q);
 #pragma unroll
-        for (int q = 0; q < IB; ++q) {  // full range: j is a constant once unrolled
-          if (q > j) {
-            const T pq = prow[q];
+          for (int s = 0; s < S; ++s) v[s][q - 1] = leaf_fms(v[s][q], l[s], u);
+        };
+        if (W > 1)
+          update(1);
+        else
 #pragma unroll
-            for (int s = 0; s < S; ++s) v[s][q] = leaf_fms(v[s][q], l[s], pq);
-          }
-        }
-      } else {
+          for (int s = 0; s < S; ++s) v[s][0] = last[s];
+        search(d + 1);
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const int r = k + t + s * PT;
-          if (r > d && r < nrows) {
-            const T l = cmul(v[s][j], inv);
-            v[s][j] = l;
+        for (int q = 2; q < W; ++q) update(q);
 #pragma unroll
-            for (int q = 0; q < IB; ++q)
-              if (q > j) v[s][q] = leaf_fms(v[s][q], l, prow[q]);
-          }
-        }
+        for (int s = 0; s < S; ++s) v[s][W - 1] = last[s];
       }
-    }
-    // the leaf's diagonal block to LDS, then the leaf back to memory (the registers of a row
-    // slot are free once it is staged)
+    };
+    block(std::integral_constant<int, 0>{});
+    if constexpr (IB / BB > 1) block(std::integral_constant<int, 1>{});
+    if constexpr (IB / BB > 2) block(std::integral_constant<int, 2>{});
+    if constexpr (IB / BB > 3) block(std::integral_constant<int, 3>{});
+    // the rows that moved, the leaf's diagonal block to LDS, and the leaf back to memory (the
+    // registers of a row slot are free once it is staged)
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const int r = k + t + s * PT;
-      if (r >= cl && r < cl + IB) {
+      const int home = t + s * PT;
+      if (pos[s] >= 0 && pos[s] != home) {
+        const int i = atomicAdd(&s_lcnt, 1);
+        s_lpos[i] = pos[s];
+        s_lorg[i] = home;
+      }
+      if (!ONE && pos[s] >= cl && pos[s] < cl + IB) {
 #pragma unroll
-        for (int q = 0; q < IB; ++q) s_L11[r - cl][q] = wide(v[s][q]);
+        for (int q = 0; q < IB; ++q) s_L11[pos[s] - cl][q] = v[s][reg_of(q)];
       }
     }
-    if constexpr (STAGE) {
-      const int ch = lane % CPR, rsub = lane / CPR;
-      int kb = k;
-      asm volatile("" : "+s"(kb));  // row addresses are formed here, not held across the leaves
+    ldx = here();
 #pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int rw = kb + s * PT + wave * 64;
-        if (rw + 64 <= cl || rw >= nrows) continue;  // uniform per wave
+    for (int s = 0; s < S; ++s) {
+      const int rw = s * PT + wave * 64;
+      if (rw >= nrows) continue;  // uniform per wave
+      s_row[t] = pos[s];
 #pragma unroll
-        for (int q = 0; q < IB; ++q) s_X[t][q] = v[s][q];
+      for (int g = 0; g < IB / SEG; ++g) {
+#pragma unroll
+        for (int q = 0; q < SEG; ++q) s_X[t][q] = v[s][reg_of(g * SEG + q)];
         wave_sync();
 #pragma unroll
         for (int u = 0; u < CPR; ++u) {
-          const int r = rw + u * RPI + rsub;
-          const T* e = s_X[wave * 64 + u * RPI + rsub] + 2 * ch;
-          const T e0 = e[0], e1 = e[1];
-          if (r >= cl && r < nrows) *(float4*)(A + r * ld + cl + 2 * ch) = make_float4(e0.x, e0.y, e1.x, e1.y);
+          const int i = wave * 64 + u * RPI + rsub, r = s_row[i];
+          const float4 x = chunk_get(s_X[i] + PER * ch);
+          if (r >= cl) *(float4*)at(r, k + cl + g * SEG + PER * ch, ldx) = x;
         }
-        wave_sync();  // read before the next slot rewrites the rows
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int r = k + t + s * PT;
-        if (r >= cl && r < nrows) store_row<IB>(A + r * ld + cl, v[s]);
+        wave_sync();  // read before the next piece rewrites the rows
       }
     }
     __syncthreads();
+    const int cnt = s_lcnt;
     // the leaf's interchanges on the other columns of the panel (whole panel rows), and on
-    // the `left` columns before it (the earlier panels of its group, see lu_factor_any),
-    // applied as one gather: at most 2 IB rows change, listed as (position, original row)
-    // pairs, moved through LDS in chunks of 2 NB - IB columns
-    if (t == 0) {
-      int cnt = IB;
-      for (int i = 0; i < IB; ++i) {
-        s_lpos[i] = cl + i;
-        s_lorg[i] = cl + i;
+    // the `left` columns before it (the earlier panels of its group, see lu_factor_any): the at
+    // most 2 IB rows that moved, 64 columns at a time, a column per lane
+    {
+      constexpr int HELD = (2 * IB + NW - 1) / NW;
+      ldx = here();
+      const int ncols = left + NB - IB;
+      unsigned short org = 0;
+      if (!ONE && t < cnt) org = s_org[s_lorg[t]];
+      for (int c0 = 0; c0 < ncols || c0 == 0; c0 += 64) {
+        const int cc = c0 + lane, cr = cc - left;
+        const int colx = cc < left ? k - left + cc : k + (cr < cl ? cr : cr + IB);
+        T held[HELD];
+#pragma unroll
+        for (int u = 0; u < HELD; ++u) {
+          const int i = wave + NW * u;
+          T x{0, 0};
+          if (i < cnt && cc < ncols) x = *at(s_lorg[i], colx, ldx);
+          held[u] = x;
+        }
+        __syncthreads();  // every source row is read before any destination row is written
+#pragma unroll
+        for (int u = 0; u < HELD; ++u) {
+          const int i = wave + NW * u;
+          if (i < cnt && cc < ncols) *at(s_lpos[i], colx, ldx) = held[u];
+        }
       }
-      for (int q = 0; q < IB; ++q) {
-        const int d = cl + q, p = s_piv[q];
-        if (p == d || p <= d || p >= nrows) continue;
-        int e = -1;
-        if (p < cl + IB) {
-          e = p - cl;
-        } else {
-          for (int i = IB; i < cnt; ++i)
-            if (s_lpos[i] == p) e = i;
-          if (e < 0) {
-            e = cnt++;
-            s_lpos[e] = p;
-            s_lorg[e] = p;
+      if (!ONE && t < cnt) s_org[s_lpos[t]] = org;
+    }
+    __syncthreads();
+    if (w > 0) {
+      // U rows of the leaf, U = L11^-1 A[leaf rows, right of the leaf], by forward substitution in FP64:
+      // eight columns per wavefront, lane = column + 8 g holding rows g, g + 8, ..; every
+      // finished row goes to the other lanes of its column by a shuffle
+      ldx = here();
+      for (int cb = wave * 8; cb < w; cb += NW * 8) {
+        constexpr int RPL = (IB + 7) / 8;
+        const int cc = cb + (lane & 7), g = lane >> 3;
+        const bool in = cc < w && g < IB;  // (always, but for leaves of four columns)
+        auto up = [&](int q) { return at(cl + g + 8 * q, k + cl + IB + cc, ldx); };
+        double2 u[RPL];
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) u[q] = in ? wide(*up(q)) : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int r = 0; r < IB - 1; ++r) {
+          const double2 ur = shfl2(u[r / 8], (lane & 7) + 8 * (r & 7));
+#pragma unroll
+          for (int q = r / 8; q < RPL; ++q) {
+            if ((q > r / 8 || g > (r & 7)) && g < IB) u[q] = leaf_fms(u[q], wide(s_L11[g + 8 * q][r]), ur);
           }
         }
-        const int tmp = s_lorg[q];
-        s_lorg[q] = s_lorg[e];
-        s_lorg[e] = tmp;
-      }
-      s_lcnt = cnt;
-    }
-    __syncthreads();
-    {
-      constexpr int CH = 2 * NB - IB;
-      const int ncols = left + NB - IB, cnt = s_lcnt;
-      for (int c0 = 0; c0 < ncols; c0 += CH) {
-        const int nc = min(CH, ncols - c0);
-        if (c0 > 0) __syncthreads();  // the previous chunk is written back
-        for (int idx = t; idx < cnt * nc; idx += PT) {
-          const int e = idx / nc, ch = idx - e * nc, cc = c0 + ch, cr = cc - left;
-          const int colx = cc < left ? k - left + cc : k + (cr < c * IB ? cr : cr + IB);
-          s_held[e][ch] = A[s_lorg[e] * ld + colx];
-        }
-        __syncthreads();
-        for (int idx = t; idx < cnt * nc; idx += PT) {
-          const int e = idx / nc, ch = idx - e * nc, cc = c0 + ch, cr = cc - left;
-          const int colx = cc < left ? k - left + cc : k + (cr < c * IB ? cr : cr + IB);
-          A[s_lpos[e] * ld + colx] = s_held[e][ch];
-        }
-      }
-    }
-    __syncthreads();
-    const int w = k + NB - cl - IB;  // panel columns right of the leaf
-    if (w > 0) {
-      // U rows of the leaf, U = L11^-1 A[cl .. cl+IB, right of the leaf], by forward
-      // substitution in FP64: one thread per column (w < 64, one wavefront), the column's IB
-      // values in registers, the entries of the leaf's unit lower triangle read alike by all
-      if (t < w) {
-        double2 u[IB];
 #pragma unroll
-        for (int q = 0; q < IB; ++q) u[q] = ld2(A + (cl + q) * ld + cl + IB + t);
-#pragma unroll
-        for (int q = 1; q < IB; ++q)
-#pragma unroll
-          for (int pp = 0; pp < q; ++pp) u[q] = leaf_fms(u[q], s_L11[q][pp], u[pp]);
-#pragma unroll
-        for (int q = 0; q < IB; ++q) {
-          st2(A + (cl + q) * ld + cl + IB + t, u[q]);
-          s_U[q][t] = u[q];
+        for (int q = 0; q < RPL; ++q) {
+          T x;
+          narrow_to(x, u[q]);
+          if (in) {
+            *up(q) = x;
+            s_U[g + 8 * q][cc] = x;
+          }
         }
       }
       __syncthreads();
@@ -492,35 +515,43 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
       // are read back from memory (stored before the barrier above), and all old values and
       // L operands of a group are loaded before its first product, so a group waits for
       // memory once instead of once per 16 x 16 tile.  The first IB columns right of the leaf
-      // are the next leaf: their results go through the wave's own rows of s_X straight into
-      // the leaf registers (the slab's old leaf values are dead by then), so the next leaf is
-      // neither stored here nor loaded again; the other columns are written back.  Rows above
-      // the leaf's last row and columns past w are masked at the load and store.
-      constexpr int CBM = (NB - IB + 15) / 16;          // 16-column blocks, at most
-      constexpr int VRB = CBM * 4 * (int)sizeof(T) / 4;  // registers per block's old values
+      // are the next leaf: where it stays on chip their results go through the wave's own rows of
+      // s_X straight into the leaf registers (the slab's old leaf values are dead by then), so
+      // the next leaf is neither stored here nor loaded again; the other columns are written
+      // back.  Rows above the leaf's last row and columns past w are masked at the load and store.
+      constexpr int CBM = (NB - IB + 15) / 16;  // 16-column blocks, at most
+      constexpr int VRB = CBM * (int)sizeof(T) + IB / 4 * (int)sizeof(T) / 4;  // registers per block
       // with the next leaf kept on chip its registers stay live through the update, so the
-      // groups are two blocks (one with four row slots or 256 threads)
-      constexpr int RBP = KEEP_NEXT ? (S >= 4 || PT == 256 ? 1 : 2) : (VRB * 4 <= 96 ? 4 : (VRB * 2 <= 96 ? 2 : 1));
-      // The 16-wide kept leaves take their L operand from LDS, which shortens their rank
-      // updates; the leaves not kept on chip would pay for its registers in occupancy or
-      // spills, and the 256-thread kernels ran their rank updates slower with it.
-      constexpr bool LOP_LDS = KEEP_NEXT && IB == 16;
+      // groups are two blocks (one with four row slots)
+      constexpr int RBP = KEEP_NEXT ? (S >= 4 ? 1 : 2) : (VRB * 4 <= 160 ? 4 : (VRB * 2 <= 160 ? 2 : 1));
+      // the kept leaves take their L operand from LDS, which shortens their rank updates
+      constexpr bool LOP_LDS = KEEP_NEXT;
       typedef StripMma<T, 1, IB> Mma;
       const int ii = lane & 15, kq = lane >> 4;
 #pragma unroll 1
       for (int s = 0; s < S; ++s) {
-        const int r0 = k + s * PT;
+        const int r0 = s * PT;
+        ldx = here();
         if constexpr (LOP_LDS) {
-          // the slab's leaf rows, the L operand of its products, into the wave's rows of s_X
-          // (read there instead of from memory; rows past the matrix hold zeros); a group's
-          // rows take the next leaf only after the group's own products have read them
+          // the slab's leaf rows, the L operand of its products, into the wave's rows of s_X (rows
+          // past the matrix hold zeros), and those that moved here from memory, where the leaf is
+          // stored; a group's rows take the next leaf only after the group's own products have
+          // read them
           wave_sync();
 #pragma unroll
           for (int ss = 0; ss < S; ++ss)
             if (ss == s) {
 #pragma unroll
-              for (int q = 0; q < IB; ++q) s_X[t][q] = v[ss][q];
+              for (int q = 0; q < IB; ++q) s_X[t][q] = v[ss][reg_of(q)];
             }
+          wave_sync();
+          const int rw = r0 + wave * 64;
+          if (lane < cnt && s_lpos[lane] >= rw && s_lpos[lane] < rw + 64) {  // cnt <= 2 IB = 32
+            const int r = s_lpos[lane];
+#pragma unroll
+            for (int u = 0; u < CPR; ++u)
+              chunk_put(s_X[wave * 64 + r - rw] + PER * u, *(const float4*)at(r, k + cl + PER * u, ldx));
+          }
           wave_sync();
         }
 #pragma unroll 1
@@ -537,14 +568,15 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
               for (int q = 0; q < IB / 4; ++q) lop[b][q] = s_X[wave * 64 + (g + b) * 16 + ii][4 * q + kq];
             } else {
 #pragma unroll
-              for (int q = 0; q < IB / 4; ++q) lop[b][q] = rl < nrows ? A[rl * ld + cl + 4 * q + kq] : T{0, 0};
+              for (int q = 0; q < IB / 4; ++q) lop[b][q] = rl < nrows ? *at(rl, k + cl + 4 * q + kq, ldx) : T{0, 0};
             }
 #pragma unroll
             for (int cb = 0; cb < CBM; ++cb)
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
                 const int row = gbase + b * 16 + Mma::row(r, lane), cc = cb * 16 + ii;
-                old[b][cb][r] = (row >= cl + IB && row < nrows && cc < w) ? A[row * ld + cl + IB + cc] : T{0, 0};
+                old[b][cb][r] =
+                    (row >= cl + IB && row < nrows && cc < w) ? *at(row, k + cl + IB + cc, ldx) : T{0, 0};
               }
           }
 #pragma unroll
@@ -556,13 +588,7 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
               if (cb * 16 >= w) continue;  // uniform
               Mma acc;
               acc.zero();
-              acc.run_regs(lop[b],
-                           [&](int kk, int cc) {
-                             T u;
-                             narrow_to(u, s_U[kk][cb * 16 + cc]);
-                             return u;
-                           },
-                           lane);
+              acc.run_regs(lop[b], [&](int kk, int cc) { return s_U[kk][min(cb * 16 + cc, NB - IB - 1)]; }, lane);
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
                 const int row = rbase + Mma::row(r, lane), cc = cb * 16 + ii;
@@ -572,7 +598,7 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
                   if (KEEP_NEXT && cc < IB)
                     s_X[row - r0][cc] = nv;
                   else
-                    A[row * ld + cl + IB + cc] = nv;
+                    *at(row, k + cl + IB + cc, ldx) = nv;
                 }
               }
             }
@@ -588,21 +614,41 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
           for (int ss = 0; ss < S; ++ss)
             if (ss == s) {
 #pragma unroll
-              for (int q = 0; q < IB; ++q) v[ss][q] = in ? s_X[t][q] : T{0, 0};
+              for (int q = 0; q < IB; ++q) v[ss][q] = sel(in, s_X[t][q], T{0, 0});
             }
           wave_sync();  // every lane has its row before the next slab writes s_X
         }
       }
     }
-    // the next leaf reads columns written above by other threads, and s_U / s_L11 /
-    // s_piv are rewritten by it
+    // the next leaf reads columns written above by other threads, and s_U / s_L11 / s_lcnt
+    // are rewritten by it
     __syncthreads();
   }
-  // The panel's NB interchanges as one permutation of at most 2 NB rows.
+  // The panel's NB interchanges as one permutation of at most 2 NB rows: entries 0 .. NB - 1 are the
+  // positions k .. k + NB - 1, the others the rows below that moved (in no particular order).
+  int32_t* lst = ip + perm_off(jd.npad, k);
+  __shared__ int s_cnt;
+  if (t == 0) s_cnt = NB;
   __syncthreads();
-  if (wave == 0) write_perm_list(k, s_pivall, s_pos, s_org, ip + perm_off(nrows, k), lane);
-  if (t == 0 && first_zero != 0) {
-    if (info[blockIdx.x] == 0) info[blockIdx.x] = first_zero;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    // with one leaf the row in slot s ended at pos[s]; with several, position t + s PT holds s_org[]
+    const int at = ONE ? pos[s] : t + s * PT;
+    if (at < 0 || at >= nrows) continue;
+    const int org = ONE ? t + s * PT : s_org[t + s * PT];
+    int i = at;
+    if (at >= NB) {
+      if (at == org) continue;
+      i = atomicAdd(&s_cnt, 1);
+    }
+    lst[2 + i] = k + at;
+    lst[2 + PERM_MAX + i] = k + org;
+  }
+  for (int q = t; q < NB; q += PT) ip[k + q] = k + s_pivall[q];
+  __syncthreads();
+  if (t == 0) {
+    lst[0] = s_cnt;
+    if (first_zero != 0 && info[blockIdx.x] == 0) info[blockIdx.x] = first_zero;
   }
 }
 
@@ -626,7 +672,6 @@ __global__ __launch_bounds__(PT) void panel_kernel(const JobDesc* jobs, int k, i
 // overwrites the blocks of L11 and U11 it is formed from (133 KB of LDS, one workgroup per
 // compute unit).  A chain of about 50 dependent steps bounds it.  FP64 storage on one system:
 // 18 us, against 83 for two 64-step substitutions one after the other.
-__device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl(v.x, src), __shfl(v.y, src)); }
 __device__ inline void lower_pair(int task, int& i, int& m) {  // (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
   i = 1 + (task >= 1) + (task >= 3);
   m = task - i * (i - 1) / 2;
@@ -1138,45 +1183,68 @@ __global__ __launch_bounds__(256) void tslu_l21_kernel(const JobDesc* jobs, int 
 // ------------------------------------------------------------------------------------
 // drivers
 // ------------------------------------------------------------------------------------
-// Leaf width: FP32 storage keeps the leaf in FP32 registers, so 16 columns fit where FP64
-// storage holds 8; wider leaves halve the passes over the rest of the panel (the
-// panel's memory traffic).  Past 2560 rows the leaf is halved to stay in registers.
+// Leaf width: up to 512 bytes of leaf per thread (FP32: 32 columns up to two row slots, 16 up to five;
+// FP64: half of that), so that two wavefronts per SIMD still hold it; past that it is halved to
+// stay in registers.
+// FP32 panels of at most small_rows (at most PANEL_SMALL_MAX = 768) rows take 256-thread
+// workgroups, two per compute unit: 320 panels of 512 rows 176 us against 258 in 512-thread
+// workgroups, of 768 rows 236 against 348 (2 panels: 118 and 116, 157 and 150).  FP64 panels do up to 256
+// rows, where one row slot holds a 32-wide leaf.
 template <typename T>
 static void launch_panel(const JobDesc* jobs, int njobs, int k, int left, int rows, T* work, int32_t* piv,
                          int32_t* info, hipStream_t s, int nopiv = 0, int small_rows = PANEL_SMALL_ROWS) {
-  constexpr int PT = 512;
-  constexpr int IBW = sizeof(T) == sizeof(float2) ? 16 : 8;
+  auto run = [&](auto pt, auto slots, auto ib) {
+    constexpr int PT = decltype(pt)::value;
+    panel_kernel<T, PT, decltype(slots)::value, decltype(ib)::value>
+        <<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv);
+  };
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  typedef std::integral_constant<int, 4> I4;
+  typedef std::integral_constant<int, 5> I5;
+  typedef std::integral_constant<int, 6> I6;
+  typedef std::integral_constant<int, 7> I7;
+  typedef std::integral_constant<int, 8> I8;
+  typedef std::integral_constant<int, 16> I16;
+  typedef std::integral_constant<int, 32> I32;
+  typedef std::integral_constant<int, 256> P256;
+  typedef std::integral_constant<int, 512> P512;
   if constexpr (sizeof(T) == sizeof(float2)) {
     if (rows <= std::min(small_rows, PANEL_SMALL_MAX)) {
-      // FP32 storage up to small_rows (at most PANEL_SMALL_MAX = 768) rows: 256-thread
-      // workgroups with 8-wide leaves fit three jobs per CU, which hides more of the short
-      // panels' barrier and shuffle latency behind another job's work (where the wider leaves
-      // of the 512-thread kernel, one job per CU, win instead is found by the autotuner; up
-      // to 2304 rows the small form was measured 1.1-1.6x slower than the large one from
-      // 1024 rows on, as more row slots per thread drop it to two and one job per CU)
-      const int S2 = (rows + 255) / 256;
-      switch (S2) {
-        case 1: panel_kernel<T, 256, 1, 8><<<njobs, 256, 0, s>>>(jobs, k, left, work, piv, info, nopiv); return;
-        case 2: panel_kernel<T, 256, 2, 8><<<njobs, 256, 0, s>>>(jobs, k, left, work, piv, info, nopiv); return;
-        default: panel_kernel<T, 256, 3, 8><<<njobs, 256, 0, s>>>(jobs, k, left, work, piv, info, nopiv); return;
+      switch ((rows + 255) / 256) {
+        case 1: return run(P256{}, I1{}, I32{});
+        case 2: return run(P256{}, I2{}, I32{});
+        default: return run(P256{}, I3{}, I16{});
       }
     }
-  }
-  const int S = (rows + PT - 1) / PT;
-  switch (S) {
-    case 1: panel_kernel<T, PT, 1, IBW><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 2: panel_kernel<T, PT, 2, IBW><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 3: panel_kernel<T, PT, 3, IBW><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 4: panel_kernel<T, PT, 4, IBW><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 5: panel_kernel<T, PT, 5, IBW><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 6: panel_kernel<T, PT, 6, IBW / 2><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    case 7: panel_kernel<T, PT, 7, IBW / 2><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
-    default: panel_kernel<T, PT, 8, IBW / 2><<<njobs, PT, 0, s>>>(jobs, k, left, work, piv, info, nopiv); break;
+    switch ((rows + 511) / 512) {
+      case 1: return run(P512{}, I1{}, I32{});
+      case 2: return run(P512{}, I2{}, I32{});
+      case 3: return run(P512{}, I3{}, I16{});
+      case 4: return run(P512{}, I4{}, I16{});
+      case 5: return run(P512{}, I5{}, I16{});
+      case 6: return run(P512{}, I6{}, I8{});
+      case 7: return run(P512{}, I7{}, I8{});
+      default: return run(P512{}, I8{}, I8{});
+    }
+  } else {
+    if (rows <= 256) return run(P256{}, I1{}, I32{});
+    switch ((rows + 511) / 512) {
+      case 1: return run(P512{}, I1{}, I32{});
+      case 2: return run(P512{}, I2{}, I16{});
+      case 3: return run(P512{}, I3{}, I8{});
+      case 4: return run(P512{}, I4{}, I8{});
+      case 5: return run(P512{}, I5{}, I8{});
+      case 6: return run(P512{}, I6{}, I4{});
+      case 7: return run(P512{}, I7{}, I4{});
+      default: return run(P512{}, I8{}, I4{});
+    }
   }
 }
 
 // The split-mode panel at k = 0 of systems of `rows` rows, for the autotuner: variant 0 the
-// 256-thread workgroups with 8-wide leaves (rows <= PANEL_SMALL_MAX), 1 the 512-thread ones.
+// 256-thread workgroups (rows <= PANEL_SMALL_MAX), 1 the 512-thread ones.
 void launch_panel_f32_variant(int variant, const JobDesc* jobs, int njobs, int rows, float2* work, int32_t* piv,
                               int32_t* info, hipStream_t s) {
   launch_panel<float2>(jobs, njobs, 0, 0, rows, work, piv, info, s, 0, variant == 0 ? PANEL_SMALL_MAX : 0);

@@ -6,7 +6,7 @@
 //   kind 0 (narrow): the update of a group's last panel, K = (G - 1) NB over
 //   (npad - (G - 1) NB) rows x NB columns;
 //   panels: the split-mode panel of a given height (its NB columns only) with 256-thread
-//   workgroups and 8-wide leaves against 512-thread workgroups and 16-wide leaves.
+//   workgroups against 512-thread workgroups.
 // Values are bounded pseudo-random numbers (an integer hash), so repeated updates stay finite.
 #include <algorithm>
 #include <vector>

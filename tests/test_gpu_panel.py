@@ -1,0 +1,67 @@
+"""The panel factorization at the edges of its shapes: heights where the workgroup size, the row
+slots per thread or the leaf width change, pivots that move every row far, ties, exact zeros."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# heights of the first panel (n rounded up to 64): one row slot of 256 and of 512 threads, 2 .. 8 slots
+SIZES = [1, 63, 64, 65, 256, 257, 320, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 2048, 2049, 2561]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2311_12134_amd as P
+    c = P.Context(0)
+    yield c
+    c.close()
+
+
+def _solve(ctx, mats, rhs, precision):
+    x = [torch.from_numpy(b).cuda() for b in rhs]
+    info = ctx.batched_lu_solve([torch.from_numpy(m).cuda() for m in mats], x, precision=precision).cpu().numpy()
+    return [v.cpu().numpy() for v in x], info
+
+
+@pytest.mark.parametrize("precision", ["fp64", "split"])
+@pytest.mark.parametrize("kind", ["reversed", "ties"])
+def test_panel_shapes(ctx, precision, kind):
+    """reversed: a well-conditioned matrix with its rows in reverse order, so that every column's pivot
+    comes from the other end; ties: entries of equal magnitude only.  The backward error of an LU with
+    partial pivoting is n eps times the growth (below 10 n^(1/2) for these)."""
+    rng = np.random.default_rng(5)
+    eps = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24
+    for lo in range(0, len(SIZES), 6):  # uneven batches
+        print("[gpu] panel shapes", kind, precision, SIZES[lo:lo + 6], flush=True)
+        mats, rhs = [], []
+        for n in SIZES[lo:lo + 6]:
+            if kind == "reversed":
+                m = (0.5 * (rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))) / np.sqrt(n) + np.eye(n))[::-1]
+            else:
+                m = np.array([1, 1j, -1, -1j])[rng.integers(0, 4, (n, n))]
+            mats.append(m.copy())
+            rhs.append(rng.normal(size=(n, 2)) + 1j * rng.normal(size=(n, 2)))
+        got, info = _solve(ctx, mats, rhs, precision)
+        for m, b, x, i in zip(mats, rhs, got, info):
+            n = len(m)
+            if kind == "ties" and i != 0:
+                assert np.linalg.matrix_rank(m) < n, n  # small ones may be singular
+                continue
+            back = np.linalg.norm(m @ x - b) / (np.linalg.norm(m) * np.linalg.norm(x))
+            assert i == 0 and back <= 10 * np.sqrt(n) * eps, (n, i, back)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "split"])
+def test_zero_pivot_is_reported_at_its_column(ctx, precision):
+    """A zero column met in the first and in the second leaf of the first and of a later panel."""
+    rng = np.random.default_rng(6)
+    cols = [0, 5, 40, 63, 64, 150, 299]
+    mats, rhs = [], []
+    for c in cols:
+        m = rng.normal(size=(300, 300)) + 1j * rng.normal(size=(300, 300))
+        m[:, c] = 0
+        mats.append(m)
+        rhs.append(np.ones((300, 1), dtype=np.complex128))
+    _, info = _solve(ctx, mats, rhs, precision)
+    assert list(info) == [c + 1 for c in cols]
