@@ -1,0 +1,55 @@
+"""When the split-mode refinement stops: at the tolerance, except that a large system which reaches it by a
+hair takes one more correction."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2311_12134_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("members,extra", [(113, False), (169, True)])
+def test_large_systems_that_just_reach_the_tolerance_are_corrected_once_more(members, extra):
+    """Systems of 1856 and 2752 rows; the tolerance is set to what a looser one was met with, plus a little.
+    A correction gains far more than the factor 10 asked for here."""
+    cells = 10
+    grid = np.array([(i, j, k) for i in range(cells) for j in range(cells) for k in range(cells)], dtype=np.float64)
+    pos = np.concatenate([grid, grid + 0.5]) * 5.7
+    d = pos - pos[0]
+    d -= np.round(d / (cells * 5.7)) * cells * 5.7
+    radius = np.sort(np.linalg.norm(d, axis=1))[members - 1] * (1 + 1e-9)
+    ctx = P.Context(0)
+    liz = P.build_liz(pos, np.eye(3) * cells * 5.7, radius, centres=[0])
+    assert liz.ptr[1] == members
+    atom, dpos = liz.to_device(ctx.device)
+    phase = torch.from_numpy(np.random.default_rng(2).uniform(-0.6, 0.6, (len(pos), 4))).cuda()
+
+    def solve(tol, **kw):
+        tp, tm, info, berr = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.0005, precision="split", refine_tol=tol, **kw)
+        assert int(info.abs().max()) == 0 and float(berr.max()) <= tol
+        return tp, berr.cpu().numpy().ravel()[:2]
+
+    _, met = solve(1e-10)  # below what FP32 factors reach without a correction
+    met = met.max()
+    print("[gpu] refinement of %d members: %.2e" % (members, met), flush=True)
+    assert met > 2e-15  # another correction shows
+    _, again = solve(1.01 * met)
+    if extra:
+        assert (again <= 0.1 * met).all()
+    else:
+        assert again.max() == met
+    # without a correction left the tolerance itself decides; the FP64 path is the reference
+    it = next(n for n in range(10) if _accepted(ctx, liz, atom, dpos, phase, 1.01 * met, n))
+    assert _accepted(ctx, liz, atom, dpos, phase, 1.01 * met, it + 1)
+    ref = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.0005, precision="fp64")[0]
+    tp, _ = solve(1e-14)
+    assert float((tp - ref).norm() / ref.norm()) <= 1e-10  # 1e-14 times the condition
+    ctx.close()
+
+
+def _accepted(ctx, liz, atom, dpos, phase, tol, corrections):
+    """Whether refinement within so many corrections reached tol (the sentinel -1 marks the FP64 fallback)."""
+    berr = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.0005, precision="split", refine_tol=tol,
+                         max_refine=corrections)[3]
+    return float(berr.cpu().numpy().ravel()[:2].min()) >= 0
