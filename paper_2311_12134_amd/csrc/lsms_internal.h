@@ -93,6 +93,16 @@ __host__ __device__ inline int64_t pair_index(int a, int b, int nb) {
   return (int64_t)a * nb - (int64_t)a * (a - 1) / 2 + (b - a);
 }
 
+#if defined(__HIPCC__)
+// A barrier that orders LDS only, for chains whose data pass through LDS: __syncthreads also waits for
+// every load ahead and every store to memory.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+#endif
+
 // The NB interchanges of one panel permute at most 2 NB rows.  The panel kernel stores
 // that permutation once per panel as (destination row, source row) pairs so that the
 // trailing update and the solves apply it as one parallel gather instead of NB

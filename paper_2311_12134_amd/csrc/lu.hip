@@ -146,13 +146,6 @@ __device__ inline void wave_sync() {
 }
 
 __device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl(v.x, src), __shfl(v.y, src)); }
-// A barrier that orders LDS only: the pivot columns' data passes through LDS, and waiting for a
-// leaf's stores to memory there would lengthen their chain.
-__device__ inline void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 // The NB interchanges of a panel starting at row k (pivall[q]: the row exchanged with
 // k + q at step q) as one permutation of at most 2 NB rows, written to lst: entries
 // 0..NB-1 are the positions k..k+NB-1, further entries the pivot rows below the panel;

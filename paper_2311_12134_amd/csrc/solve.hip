@@ -10,10 +10,10 @@
 // Panels come in groups of G (2 .. 4, as the factorization had them: the L rows of a
 // panel are stored after the permutations of the later panels of its group) and every group
 // costs two launches over the whole batch:
-//   solve_group_diag_kernel    one workgroup per job: panel by panel, the permutation (a
-//                              gather of at most 2 NB rows), the coupling blocks with the
-//                              group's panels solved before it, and the NB x NB diagonal step
-//                              as a product with the stored inverse (or its transpose);
+//   solve_group_diag_kernel    one workgroup per job: the group's permutations in one gather, then
+//                              panel by panel the NB x NB diagonal step as a product with the
+//                              stored inverse (or its transpose) and the coupling blocks of the
+//                              panels still to come with it;
 //   solve_group_update_kernel  one workgroup per (64-row strip, job): the strip against the
 //                              group's G NB solved rows (K = G NB) on the matrix cores,
 //                              operands read straight from the factors (FP32 factors widened in
@@ -71,31 +71,71 @@ __device__ inline float2 xminus(float2 x, double2 v) { return make_float2(x.x - 
 __device__ inline void xput(double2& d, double2 v) { d = v; }
 __device__ inline void xput(float2& d, double2 v) { d = make_float2((float)v.x, (float)v.y); }
 
-// One panel permutation of the solution rows (at most PERM_MAX (dst, src) pairs): every
-// source row is read into registers before any destination row is written.
-template <int NRHS, typename XT>
-__device__ inline void apply_perm(const int32_t* lst, bool inverse, XT* X, int* s_dst, int* s_src, int t) {
-  constexpr int HELD = PERM_MAX * NRHS / 256;
-  const int cnt = lst[0];
-  for (int i = t; i < cnt; i += 256) {
-    s_dst[i] = lst[2 + i];
-    s_src[i] = lst[2 + PERM_MAX + i];
+// The permutations of a group's panels, as one: every moved row's source is traced back through
+// the panels' lists (one hash table of destinations per list), so the solution rows are
+// gathered and scattered once instead of once per panel.  lists(o) is the o-th list in the
+// order of application, inverse takes (source, destination) pairs for (destination, source).
+// NT threads; every source row is read into registers before any destination row is written.
+constexpr int HASH_BITS = 8, HASH = 1 << HASH_BITS;  // slots of a table
+static_assert(HASH >= 2 * PERM_MAX, "at most half of the slots taken");
+struct PermScratch {
+  int key[4][HASH], val[4][HASH];
+  int dst[4 * PERM_MAX], src[4 * PERM_MAX];
+};
+template <int NRHS, int NT, typename XT, typename LIST>
+__device__ inline void apply_perms(LIST lists, int np, bool inverse, XT* X, PermScratch& ps, int t) {
+  static_assert((NT / 256) * PERM_MAX <= NT, "one entry per thread");
+  constexpr int G = NT / 256, LD = XView<XT>::LD;
+  // multiplicative: a panel's 64 rows would be one run of taken slots under a mask, 20 us to walk
+  auto slot = [](int row) { return (int)(((unsigned)row * 2654435761u) >> (32 - HASH_BITS)); };
+  const int o = t / PERM_MAX, i = t % PERM_MAX;
+  int to = -1, from = -1;
+  if (o < np) {
+    const int32_t* lst = lists(o);
+    const int cnt = lst[0], a = lst[2 + i], b = lst[2 + PERM_MAX + i];  // entries past cnt are not used
+    if (i < cnt) {
+      to = inverse ? b : a;
+      from = inverse ? a : b;
+    }
+  }
+  for (int q = t; q < G * HASH; q += NT) ps.key[q / HASH][q % HASH] = -1;
+  __syncthreads();
+  if (to >= 0) {
+    int h = slot(to);
+    while (atomicCAS(&ps.key[o][h], -1, to) != -1) h = (h + 1) & (HASH - 1);  // destinations of a list differ
+    ps.val[o][h] = from;
   }
   __syncthreads();
-  const int* from = inverse ? s_dst : s_src;
-  const int* to = inverse ? s_src : s_dst;
-  constexpr int LD = XView<XT>::LD;
+  auto find = [&](int l, int row) {
+    int h = slot(row), k;
+    while ((k = ps.key[l][h]) != -1 && k != row) h = (h + 1) & (HASH - 1);
+    return k == -1 ? -1 : ps.val[l][h];
+  };
+  if (to >= 0) {
+    for (int l = o - 1; l >= 0; --l) {
+      const int f = find(l, from);
+      if (f >= 0) from = f;
+    }
+    for (int l = o + 1; l < np; ++l)
+      if (find(l, to) >= 0) to = -1;  // a later list writes this row
+  }
+  if (t < G * PERM_MAX) {
+    ps.dst[t] = to;
+    ps.src[t] = from;
+  }
+  __syncthreads();
+  constexpr int HELD = G * PERM_MAX * NRHS / NT;
   XT held[HELD];
 #pragma unroll
   for (int u = 0; u < HELD; ++u) {
-    const int idx = t + 256 * u, i = idx / NRHS, c = idx % NRHS;
-    held[u] = i < cnt ? X[(int64_t)from[i] * LD + c] : XT{};
+    const int idx = t + NT * u, e = idx / NRHS, c = idx % NRHS;
+    held[u] = ps.dst[e] >= 0 ? X[(int64_t)ps.src[e] * LD + c] : XT{};
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < HELD; ++u) {
-    const int idx = t + 256 * u, i = idx / NRHS, c = idx % NRHS;
-    if (i < cnt) X[(int64_t)to[i] * LD + c] = held[u];
+    const int idx = t + NT * u, e = idx / NRHS, c = idx % NRHS;
+    if (ps.dst[e] >= 0) X[(int64_t)ps.dst[e] * LD + c] = held[u];
   }
   __syncthreads();
 }
@@ -109,114 +149,116 @@ __device__ inline void apply_perm(const int32_t* lst, bool inverse, XT* X, int* 
 // LDS stage, no barriers in the update.
 // ------------------------------------------------------------------------------------
 
-// Element (q, p) of an operator on a panel's rows at kp, from the stored diagonal block:
-// the inverse of the unit lower triangle (unit diagonal implied) or of the upper one.
-template <typename XT, typename T>
-__device__ inline XT lower_inv(const T* A, int64_t ld, int kp, int q, int p) {
-  return p < q ? fac<XT>(A + (int64_t)(kp + q) * ld + kp + p) : XT{p == q ? 1.0f : 0.0f, 0.0f};
-}
-template <typename XT, typename T>
-__device__ inline XT upper_inv(const T* A, int64_t ld, int kp, int q, int p) {
-  return p >= q ? fac<XT>(A + (int64_t)(kp + q) * ld + kp + p) : XT{};
-}
-
-// Y (64 x NRHS) = op (64 x 64) Xin (64 x NRHS in LDS): wave w forms rows 16w .. 16w+16 and
-// hands each element to put(row, column, value).
-template <int NRHS, typename XT, typename OP, typename PUT>
-__device__ inline void panel_product(OP op, const XT (*xin)[NRHS], PUT put, int wave, int lane) {
-  StripMma<XT, NRHS / 16> y;
-  y.zero();
-  y.run([&](int i, int kk) { return op(wave * 16 + i, kk); }, [&](int kk, int c) { return xin[kk][c]; }, lane);
-  const int ii = lane & 15;
-#pragma unroll
-  for (int cb = 0; cb < NRHS / 16; ++cb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) put(wave * 16 + y.row(r, lane), cb * 16 + ii, y.value(cb, r));
-}
-
-template <typename T, typename XT, int NRHS, int MODE>
-__global__ __launch_bounds__(256) void solve_group_diag_kernel(const JobDesc* jobs, int k, int group, const T* work,
-                                                               const int32_t* piv, double2* xbuf, int64_t col_off,
-                                                               const int32_t* skip) {
+// The group's diagonal step: one wavefront per 16 rows of the group (4 G wavefronts).  Panel j's
+// wavefronts form X_j = inv_j (X_j - sum of couplings), the wavefronts of the panels still to come
+// then subtract their coupling with X_j, in accumulators that they keep, so a group is 2 G
+// dependent 16 x 64 products on each wavefront's own rows, with a barrier after each.
+// Sixteen columns a workgroup (blockIdx.y); 32 would not fit the registers of sixteen wavefronts.
+// Bound by latency (a group holds 10 products of 64 x 64 x NRHS): the factors do not depend on
+// the solution, so a wavefront's operands load a product ahead (FP32 factors in a second register
+// set; FP64 factors into the set just used, while the other panels' wavefronts work), 64 consecutive
+// bytes of a row per instruction.  A forward and a back step of four panels, n = 2176, against
+// four wavefronts that went through the ten products one by one, each loading its own operands:
+// FP32 on 6 systems 53 -> 24 and 22 us, FP64 on 2 46 -> 38; on 250 (n = 1984) 83 -> 60 and 77 -> 57,
+// where the blocks' scattered rows from memory bound it (neither two workgroups a compute unit, nor
+// touching the lines ahead, nor other offsets between the systems changed that).
+template <typename T, typename XT, int MODE, int G>
+__global__ __launch_bounds__(256 * G) void solve_group_diag_kernel(const JobDesc* jobs, int k, const T* work,
+                                                                   const int32_t* piv, double2* xbuf, int64_t col_off,
+                                                                   const int32_t* skip) {
   const int job = blockIdx.x;
   if (skip && skip[job]) return;
   const JobDesc jd = jobs[job];
   if (k >= jd.npad) return;  // uniform
+  constexpr bool TRANS = MODE == MODE_UT || MODE == MODE_LT, FORWARD = MODE == MODE_L || MODE == MODE_UT;
+  constexpr bool LOWER = MODE == MODE_L || MODE == MODE_LT, AHEAD = sizeof(T) == sizeof(float2);
   const T* A = work + jd.a_off;
   const int64_t ld = jd.npad;
-  const int32_t* pv = piv + jd.piv_off;
-  XT* X = XView<XT>::base(xbuf, jd, col_off);
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int np = min(group, (jd.npad - k) / NB);  // panels of the group inside this job
-  auto kp = [&](int j) { return k + j * NB; };
-  __shared__ XT s_a[NB][NRHS];
-  __shared__ XT s_b[NB][NRHS];
-  __shared__ int s_dst[PERM_MAX], s_src[PERM_MAX];
-  auto xrow = [&](int r) { return X + (int64_t)r * XView<XT>::LD; };
-  auto load = [&](XT (*dst)[NRHS], int r0) {
-    for (int idx = t; idx < NB * NRHS; idx += 256) dst[idx / NRHS][idx % NRHS] = xrow(r0 + idx / NRHS)[idx % NRHS];
+  constexpr int NRHS = 16;
+  XT* X = XView<XT>::base(xbuf, jd, col_off + NRHS * blockIdx.y);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int np = min(G, (jd.npad - k) / NB);  // panels of the group inside this job
+  const int b = wave >> 2, row0 = (wave & 3) * 16;  // this wavefront's panel and its rows in it
+  const int ii = lane & 15, kq = lane >> 4;
+  constexpr int XLD = NRHS + (sizeof(XT) == sizeof(float2) ? 8 : 0);  // FP32: the lane quarters read 2 rows apart, in two bank halves
+  __shared__ XT s_a[NB * XLD];
+  __shared__ XT s_x[NB * XLD];
+  auto list = [&](int o) {
+    return piv + jd.piv_off + perm_off(jd.npad, k + (MODE == MODE_LT ? np - 1 - o : o) * NB);
   };
-  auto to_x = [&](int r0) {  // result rows to the solution
-    return [=](int row, int c, double2 v) { xput(xrow(r0 + row)[c], v); };
+  __shared__ PermScratch ps;  // MODE_L and MODE_LT
+  // the k of step q in lane quarter h: four quarters' 16-byte pieces side by side
+  auto kof = [](int q, int h) { return sizeof(T) == sizeof(float2) ? 8 * (q >> 1) + 2 * h + (q & 1) : 4 * q + h; };
+  // Panel i's block of this wavefront's rows: lane's row ii, its sixteen k's (i == b: the diagonal block)
+  auto load = [&](T* a, int i) {
+    const int r = k + b * NB + row0, c = k + i * NB;
+    const T* p = TRANS ? A + (int64_t)c * ld + r : A + (int64_t)r * ld + c;  // uniform
+    const int mine = TRANS ? kof(0, kq) * (int)ld + ii : ii * (int)ld + kof(0, kq);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) a[q] = (p + kof(q, 0) * (TRANS ? ld : 1))[mine];
   };
-  // rows of s_a minus a product: each wave updates only its own rows, after its product
-  auto minus_into_a = [&](int row, int c, double2 v) { s_a[row][c] = xminus(s_a[row][c], v); };
-  // s_a -= op (64 x 64) times the solved rows of panel i, staged through s_b
-  auto couple = [&](int i, auto op) {
-    __syncthreads();
-    load(s_b, kp(i));
-    __syncthreads();
-    panel_product<NRHS, XT>(op, s_b, minus_into_a, wave, lane);
+  auto order = [&](int o) { return FORWARD ? o : np - 1 - o; };
+  const bool active = b < np;
+  const int pos = order(b);  // the step at which this wavefront's panel is solved
+  typedef StripMma<XT, 1> Mma;
+  T buf[2][16];  // the operand of step o is in buf[o & 1] with AHEAD, else in buf[0]
+  if (active) load(buf[0], order(0));
+  if constexpr (MODE == MODE_L) apply_perms<NRHS, 256 * G>(list, np, false, X, ps, t);
+  auto xrow = [&](int r) { return X + (int64_t)(k + b * NB + row0 + r) * XView<XT>::LD; };
+  auto slot = [&](int r) { return (row0 + r) * XLD + ii; };
+  XT x0[4];
+  Mma y;
+  y.zero();
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x0[r] = xrow(Mma::row(r, lane))[ii];
+  }
+  auto product = [&](Mma& m, const T* a, const XT* xin) {
+    XT w[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) w[q] = fac<XT>(a + q);
+    m.run_regs(w, [&](int kk, int c) { return xin[kof(kk >> 2, kk & 3) * XLD + c]; }, lane);
   };
-  if (MODE == MODE_L) {
-    // panel by panel: P_j (the earlier panels' L rows are stored after it), the couplings
-    // L[j, i] with the earlier panels of the group, L_j^-1
-    for (int j = 0; j < np; ++j) {
-      if (j > 0) __syncthreads();
-      apply_perm<NRHS, XT>(pv + perm_off(jd.npad, kp(j)), false, X, s_dst, s_src, t);
-      load(s_a, kp(j));
-      for (int i = 0; i < j; ++i)
-        couple(i, [&](int q, int p) { return fac<XT>(A + (int64_t)(kp(j) + q) * ld + kp(i) + p); });
-      __syncthreads();
-      panel_product<NRHS, XT>([&](int q, int p) { return lower_inv<XT>(A, ld, kp(j), q, p); }, s_a, to_x(kp(j)),
-                              wave, lane);
+#pragma unroll
+  for (int o = 0; o < G; ++o) {
+    if (o >= np) break;  // uniform
+    T* cur = buf[AHEAD ? o & 1 : 0];
+    if (active && o == pos) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_a[slot(Mma::row(r, lane))] = xminus(x0[r], y.value(0, r));
     }
-  } else if (MODE == MODE_U) {
-    // last panel first: the couplings U[j, i] with the later panels, U_j^-1
-    for (int j = np - 1; j >= 0; --j) {
-      __syncthreads();
-      load(s_a, kp(j));
-      for (int i = j + 1; i < np; ++i)
-        couple(i, [&](int q, int p) { return fac<XT>(A + (int64_t)(kp(j) + q) * ld + kp(i) + p); });
-      __syncthreads();
-      panel_product<NRHS, XT>([&](int q, int p) { return upper_inv<XT>(A, ld, kp(j), q, p); }, s_a, to_x(kp(j)),
-                              wave, lane);
+    lds_barrier();
+    if (active && o == pos) {
+      // the diagonal block holds the inverses of both triangles: the other one's entries drop out,
+      // and the unit lower triangle's diagonal is not stored
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int kk = kof(q, kq), r = row0 + ii;
+        const bool mine = MODE == MODE_L ? kk < r : MODE == MODE_LT ? kk > r : MODE == MODE_U ? kk >= r : kk <= r;
+        cur[q].x = mine ? cur[q].x : LOWER && kk == r ? 1 : 0;
+        cur[q].y = mine ? cur[q].y : 0;
+      }
+      y.zero();
+      product(y, cur, s_a);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        XT v;
+        xput(v, y.value(0, r));
+        s_x[slot(Mma::row(r, lane))] = v;
+        xrow(Mma::row(r, lane))[ii] = v;
+      }
     }
-  } else if (MODE == MODE_UT) {
-    // first panel first: the couplings U[i, j]^T with the earlier panels, U_j^-T
-    for (int j = 0; j < np; ++j) {
-      __syncthreads();
-      load(s_a, kp(j));
-      for (int i = 0; i < j; ++i)
-        couple(i, [&](int q, int p) { return fac<XT>(A + (int64_t)(kp(i) + p) * ld + kp(j) + q); });
-      __syncthreads();
-      panel_product<NRHS, XT>([&](int q, int p) { return upper_inv<XT>(A, ld, kp(j), p, q); }, s_a, to_x(kp(j)),
-                              wave, lane);
+    if (o + 1 == np) break;  // uniform
+    lds_barrier();
+    if (active && o < pos) {
+      if (AHEAD) load(buf[(o + 1) & 1], order(o + 1));
+      product(y, cur, s_x);
+      if (!AHEAD) load(cur, order(o + 1));
     }
-  } else {
-    // MODE_LT, last panel first: the couplings L[i, j]^T with the later panels, L_j^-T; then
-    // the group's permutations inverted, last panel's first
-    for (int j = np - 1; j >= 0; --j) {
-      __syncthreads();
-      load(s_a, kp(j));
-      for (int i = j + 1; i < np; ++i)
-        couple(i, [&](int q, int p) { return fac<XT>(A + (int64_t)(kp(i) + p) * ld + kp(j) + q); });
-      __syncthreads();
-      panel_product<NRHS, XT>([&](int q, int p) { return lower_inv<XT>(A, ld, kp(j), p, q); }, s_a, to_x(kp(j)),
-                              wave, lane);
-    }
+  }
+  if constexpr (MODE == MODE_LT) {
     __syncthreads();
-    for (int j = np - 1; j >= 0; --j) apply_perm<NRHS, XT>(pv + perm_off(jd.npad, kp(j)), true, X, s_dst, s_src, t);
+    apply_perms<NRHS, 256 * G>(list, np, true, X, ps, t);
   }
 }
 
@@ -361,7 +403,14 @@ static void solve_all(const JobDesc* jobs, int njobs, int npad_max, const T* wor
   const int last = ((npad_max - 1) / GW) * GW;  // start of the last group
   auto diag = [&](auto mode_tag, int k) {
     constexpr int MODE = decltype(mode_tag)::value;
-    solve_group_diag_kernel<T, XT, NRHS, MODE><<<njobs, 256, 0, s>>>(jobs, k, group, work, piv, x, col_off, skip);
+    auto launch = [&](auto g) {
+      constexpr int G = decltype(g)::value;
+      solve_group_diag_kernel<T, XT, MODE, G>
+          <<<dim3(njobs, NRHS / 16), 256 * G, 0, s>>>(jobs, k, work, piv, x, col_off, skip);
+    };
+    static_assert(GROUP_MAX == 4, "groups of 2 .. 4 panels");
+    group == 2 ? launch(std::integral_constant<int, 2>{}) : group == 3 ? launch(std::integral_constant<int, 3>{})
+                                                                       : launch(std::integral_constant<int, 4>{});
   };
   auto update = [&](auto mode_tag, int k, int strips) {
     constexpr int MODE = decltype(mode_tag)::value;
