@@ -655,20 +655,20 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
 // thereby become products on the matrix cores.  No later interchange touches the block (pivots
 // of later panels lie below it), and nothing else reads U11.
 //
-// Blocked in 16 x 16 blocks (indices i, m in 0..3): one wavefront per diagonal block forms
-// X_ii = L_ii^-1 or Y_ii = U_ii^-1 (16-step FP64 substitutions), then the off-diagonal blocks
-// follow from FP64 matrix-core products:
-//   X_ij = -sum_{j <= m < i} (X_ii L_im) X_mj,   Y_ij = -sum_{i < m <= j} (Y_ii U_im) Y_mj,
-// first the six products W = X_ii L_im and the six Y_ii U_im, then the blocks one, two and
-// three steps off the diagonal (waves 0-3 the lower triangle, 4-7 the upper one).  Results
-// are kept in FP64 and rounded once to the storage precision at the store.  With FP64 storage W
-// overwrites the blocks of L11 and U11 it is formed from (133 KB of LDS, one workgroup per
-// compute unit).  A chain of about 50 dependent steps bounds it.  FP64 storage on one system:
-// 18 us, against 83 for two 64-step substitutions one after the other.
-__device__ inline void lower_pair(int task, int& i, int& m) {  // (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
-  i = 1 + (task >= 1) + (task >= 3);
-  m = task - i * (i - 1) / 2;
-}
+// Blocked in 16 x 16 blocks: one wavefront per diagonal block forms X_ii = L_ii^-1 or
+// Y_ii = U_ii^-1 (16-step FP64 substitutions, the sixteen pivots inverted beforehand side by side),
+// then the off-diagonal blocks follow from FP64 matrix-core products, for two halves within each
+// 32 x 32 triangle and then for the 32 x 32 block between them:
+//   X_ij = -X_ii (L_ij X_jj),  (i, j) = (1, 0), (3, 2);
+//   W_ij = sum_m L_im X_mj,  X_ij = -sum_m X_im W_mj,  i = 2, 3, j = 0, 1;
+// the upper triangle is the same with its blocks counted from the end.  Waves 0 - 3 take the lower
+// triangle, 4 - 7 the upper one in opposite order, so that a SIMD's two wavefronts have three
+// products together where one has one and the other two.  A first product is the operand of the second
+// without leaving its registers (accumulators and right operands have one layout).  Results
+// are kept in FP64 and rounded once to the storage precision at the store.
+// A chain of about 50 dependent steps bounds it.  FP64 storage on one system: 12 us, against 18 with
+// divisions in the substitution and one diagonal of blocks after the other (8 products deep on the
+// busiest SIMD's two wavefronts), and 83 for two 64-step substitutions.
 template <typename T>
 __global__ __launch_bounds__(512) void linv_kernel(const JobDesc* jobs, int k, T* work) {
   constexpr int B = 16;
@@ -677,17 +677,9 @@ __global__ __launch_bounds__(512) void linv_kernel(const JobDesc* jobs, int k, T
   T* A = work + jd.a_off;
   const int64_t ld = jd.npad;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  constexpr bool IN_PLACE = sizeof(T) == sizeof(double2);
-  __shared__ T s_T[NB][NB + 1];                // L11 \ U11 as factored
-  __shared__ double2 s_V[NB][NB + 1];          // X = L11^-1 below the diagonal, Y = U11^-1 on and above
-  __shared__ double2 s_W[2][IN_PLACE ? 1 : 6][B][B + 1];  // X_ii L_im (index i (i - 1) / 2 + m) and Y_mm U_mi
-  // entry (r, c) of W_im (lower, i > m) or of Y_mm U_mi (upper)
-  auto w_at = [&](bool low, int i, int m, int r, int c) -> double2& {
-    if constexpr (IN_PLACE)
-      return low ? s_T[i * B + r][m * B + c] : s_T[m * B + r][i * B + c];
-    else
-      return s_W[low ? 0 : 1][i * (i - 1) / 2 + m][r][c];
-  };
+  __shared__ T s_T[NB][NB + 1];        // L11 \ U11 as factored
+  __shared__ double2 s_V[NB][NB + 1];  // X = L11^-1 below the diagonal, Y = U11^-1 on and above
+  __shared__ double2 s_W[2][2][B][B + 1];  // W_2j of either triangle
   for (int idx = t; idx < NB * NB; idx += 512) {
     const int q = idx / NB, pp = idx % NB;
     s_T[q][pp] = A[(k + q) * ld + k + pp];
@@ -715,9 +707,11 @@ __global__ __launch_bounds__(512) void linv_kernel(const JobDesc* jobs, int k, T
       for (int j = 0; j < 4; ++j)
         if (g + 4 * j > c) s_V[o + g + 4 * j][o + c] = x[j];
     } else {
+      const double2 inv = cinv(ld2(&s_T[o + c][o + c]));
 #pragma unroll
       for (int q = B - 1; q >= 0; --q) {  // y_q /= U_qq, then broadcast it up its column
-        if (g == (q & 3)) x[q / 4] = cmul(x[q / 4], cinv(ld2(&s_T[o + q][o + q])));
+        const double2 iq = shfl2(inv, q);
+        if (g == (q & 3)) x[q / 4] = cmul(x[q / 4], iq);
         const double2 yq = shfl2(x[q / 4], (q & 3) * 16 + c);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -732,58 +726,62 @@ __global__ __launch_bounds__(512) void linv_kernel(const JobDesc* jobs, int k, T
   }
   __syncthreads();
   typedef StripMma<double2, 1, B> Mma;
-  // the inverted diagonal block d as an operand (unit diagonal of X implied, zeros outside)
-  auto diag_at = [&](int d, int r, int cc) -> double2 {
-    const int o = d * B;
-    if (lower) return r > cc ? s_V[o + r][o + cc] : make_double2(r == cc ? 1.0 : 0.0, 0.0);
-    return r <= cc ? s_V[o + r][o + cc] : make_double2(0.0, 0.0);
+  const int w4 = lower ? wave : 7 - wave;                        // this wavefront's place in its triangle
+  auto org = [&](int b) { return (lower ? b : 3 - b) * B; };     // first row or column of its block b
+  // the inverted diagonal block b (unit diagonal of X implied, zeros outside) and others as operands
+  auto D = [&](int b) {
+    return [&, o = org(b)](int r, int cc) -> double2 {
+      const bool in = lower ? r > cc : r <= cc;
+      return in ? s_V[o + r][o + cc] : make_double2(lower && r == cc ? 1.0 : 0.0, 0.0);
+    };
   };
-  // W products: lower X_ii L_im (i > m), upper Y_mm U_mi (m < i), six each over four waves
-  for (int task = wave & 3; task < 6; task += 4) {
-    int i, m;
-    lower_pair(task, i, m);
-    Mma acc;
-    acc.zero();
-    if (lower)
-      acc.run([&](int r, int kk) { return diag_at(i, r, kk); },
-              [&](int kk, int cc) { return ld2(&s_T[i * B + kk][m * B + cc]); }, lane);
-    else
-      acc.run([&](int r, int kk) { return diag_at(m, r, kk); },
-              [&](int kk, int cc) { return ld2(&s_T[m * B + kk][i * B + cc]); }, lane);
+  auto V = [&](int i, int j) { return [&, a = org(i), b = org(j)](int r, int cc) { return s_V[a + r][b + cc]; }; };
+  auto F = [&](int i, int j) { return [&, a = org(i), b = org(j)](int r, int cc) { return ld2(&s_T[a + r][b + cc]); }; };
+  auto times = [&](Mma& acc, auto a_at, const Mma& w) {  // acc += a w, w in its accumulators
 #pragma unroll
-    for (int r = 0; r < 4; ++r) w_at(lower, i, m, Mma::row(r, lane), c) = acc.value(0, r);
+    for (int q = 0; q < 4; ++q) {
+      const double2 a = a_at(c, 4 * q + g), b = w.value(0, q);
+      acc.re[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, acc.re[0], 0, 0, 0);
+      acc.im[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, acc.im[0], 0, 0, 0);
+      acc.re[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, acc.re[0], 0, 0, 0);
+      acc.im[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, acc.im[0], 0, 0, 0);
+    }
+  };
+  auto put = [&](const Mma& acc, int i, int j) {  // block (i, j) = -acc
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 v = acc.value(0, r);
+      s_V[org(i) + Mma::row(r, lane)][org(j) + c] = make_double2(-v.x, -v.y);
+    }
+  };
+  if (w4 < 2) {
+    const int i = 2 * w4 + 1, j = 2 * w4;
+    Mma w, x;
+    w.zero();
+    w.run(F(i, j), D(j), lane);
+    x.zero();
+    times(x, D(i), w);
+    put(x, i, j);
   }
   __syncthreads();
-  // blocks dd steps off the diagonal: lower X_{i, i-dd}, upper Y_{i-dd, i}, i = dd .. 3
-#pragma unroll 1
-  for (int dd = 1; dd < 4; ++dd) {
-    const int i = dd + (wave & 3);
-    if (i < 4) {
-      const int j = i - dd;
-      Mma acc;
-      acc.zero();
-      for (int m = j; m < i; ++m) {  // lower: W_im X_mj; upper: (Y_jj U_jm... ) as W(j, m) Y_mi
-        if (lower)
-          acc.run([&](int r, int kk) { return w_at(true, i, m, r, kk); },
-                  [&](int kk, int cc) { return m == j ? diag_at(j, kk, cc) : s_V[m * B + kk][j * B + cc]; }, lane);
-        else {
-          const int mm = m + 1;  // Y_{j, i} = -sum_{j < mm <= i} (Y_jj U_{j mm}) Y_{mm, i}
-          acc.run([&](int r, int kk) { return w_at(false, mm, j, r, kk); },
-                  [&](int kk, int cc) { return mm == i ? diag_at(i, kk, cc) : s_V[mm * B + kk][i * B + cc]; }, lane);
-        }
-      }
+  {
+    const int i = 2 + (w4 >> 1), j = w4 & 1;
+    double2(*const w2)[B + 1] = s_W[lower ? 0 : 1][j];
+    Mma w, x;
+    w.zero();
+    w.run(F(i, j), D(j), lane);
+    if (j == 0) w.run(F(i, 1), V(1, 0), lane);
+    x.zero();
+    if (i == 2) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double2 v = acc.value(0, r);
-        const int rr = Mma::row(r, lane);
-        if (lower)
-          s_V[i * B + rr][j * B + c] = make_double2(-v.x, -v.y);
-        else
-          s_V[j * B + rr][i * B + c] = make_double2(-v.x, -v.y);
-      }
+      for (int r = 0; r < 4; ++r) w2[Mma::row(r, lane)][c] = w.value(0, r);
     }
     __syncthreads();
+    times(x, D(i), w);
+    if (i == 3) x.run(V(3, 2), [&](int r, int cc) { return w2[r][cc]; }, lane);
+    put(x, i, j);
   }
+  __syncthreads();
   for (int idx = t; idx < NB * NB; idx += 512) {
     const int q = idx / NB, pp = idx % NB;
     st2(A + (k + q) * ld + k + pp, s_V[q][pp]);
