@@ -850,9 +850,13 @@ __global__ __launch_bounds__(256, sizeof(T) == sizeof(float2) ? 4 : 2) void swap
     }
   }
   const int ii = lane & 15;
-  const int row0 = k + wave * 16;  // this wavefront's 16 panel rows
+  // this wavefront's 16 panel rows: a strip's last product is as long as its place in the triangle, so
+  // the strips rotate with the tile, for the wavefronts of one SIMD to take a mix (250 FP32 systems of
+  // n = 1472 357 -> 344 us, 160 FP64 ones of 2176 339 -> 320 without delayed updates)
+  const int strip = (wave + blockIdx.x) & 3;
+  const int row0 = k + strip * 16;
   if (SECOND) {
-    // s_X -= L[k.., kl..k) U[kl.., col0..], kl = k - nprev NB: wave w owns rows 16w .. 16w+16.
+    // s_X -= L[k.., kl..k) U[kl.., col0..], kl = k - nprev NB: a wave owns its strip's 16 rows.
     StripMma<T, 4, sizeof(T) == sizeof(float2) ? NB / 2 : NB> d;
     d.zero();
     if constexpr (sizeof(T) == sizeof(float2)) {
@@ -863,7 +867,7 @@ __global__ __launch_bounds__(256, sizeof(T) == sizeof(float2) ? 4 : 2) void swap
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) xs[cb][r] = s_X[wave * 16 + d.row(r, lane)][cb * 16 + ii];
+        for (int r = 0; r < 4; ++r) xs[cb][r] = s_X[strip * 16 + d.row(r, lane)][cb * 16 + ii];
       constexpr int P4 = 64 * (int)sizeof(T) / 16;  // 16-byte pieces per row of the block
 #pragma unroll 1
       for (int q = 0; q < nprev; ++q) {
@@ -890,7 +894,7 @@ __global__ __launch_bounds__(256, sizeof(T) == sizeof(float2) ? 4 : 2) void swap
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          S* xp = &s_X[wave * 16 + d.row(r, lane)][cb * 16 + ii];
+          S* xp = &s_X[strip * 16 + d.row(r, lane)][cb * 16 + ii];
           st2(xp, csub(wide(xs[cb][r]), d.value(cb, r)));
         }
     } else {
@@ -907,7 +911,7 @@ __global__ __launch_bounds__(256, sizeof(T) == sizeof(float2) ? 4 : 2) void swap
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          S* xp = &s_X[wave * 16 + d.row(r, lane)][cb * 16 + ii];
+          S* xp = &s_X[strip * 16 + d.row(r, lane)][cb * 16 + ii];
           st2(xp, csub(ld2(xp), d.value(cb, r)));
         }
     }
@@ -915,19 +919,23 @@ __global__ __launch_bounds__(256, sizeof(T) == sizeof(float2) ? 4 : 2) void swap
   // U12 = L11^-1 A12 straight from the accumulators to the panel rows (the inverse is
   // stored below the diagonal; its unit diagonal and zero upper part are implied).  The
   // lane's sixteen inverse entries are loaded before the barrier, in one batch.
-  T li[NB / 4];
+  T li[4][4];  // [16 columns][step]; columns past the strip's own rows are zero and drop out
   {
-    const int q = wave * 16 + ii;
+    const int q = strip * 16 + ii;
 #pragma unroll
-    for (int s4 = 0; s4 < NB / 4; ++s4) {
-      const int kk = 4 * s4 + (lane >> 4);
-      li[s4] = kk < q ? A[(int64_t)(k + q) * ld + k + kk] : T{kk == q ? 1.0f : 0.0f, 0.0f};
-    }
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) {
+        const int kk = kb * 16 + 4 * s4 + (lane >> 4);
+        li[kb][s4] = kk < q ? A[(int64_t)(k + q) * ld + k + kk] : T{kk == q ? 1.0f : 0.0f, 0.0f};
+      }
   }
   __syncthreads();
-  StripMma<T, 4> u;
+  StripMma<T, 4, 16> u;
   u.zero();
-  u.run_regs(li, [&](int kk, int c) { return s_X[kk][c]; }, lane);
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb)
+    if (kb <= strip) u.run_regs(li[kb], [&](int kk, int c) { return s_X[kb * 16 + kk][c]; }, lane);
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
@@ -1148,27 +1156,50 @@ __global__ __launch_bounds__(256) void tslu_apply_kernel(const JobDesc* jobs, in
 
 // L21 = A21 U11^-1 below the diagonal block (U11^-1 on and above the block's diagonal,
 // written by the inverse kernel): wave w of workgroup (x, job) takes rows k + NB + 64 x + 16 w.
+// Bound by latency and memory (64 KB of L21 a workgroup): every load is issued before the first
+// product, U11^-1 comes once per workgroup through LDS (four wavefronts read it), and its zero
+// blocks are left out (10 of 16).  23 launches on 125 systems of n = 1472: 87 -> 58 us each; 8
+// of 15,440: 41 -> 27.
 template <typename T>
 __global__ __launch_bounds__(256) void tslu_l21_kernel(const JobDesc* jobs, int k, T* work) {
   const JobDesc jd = jobs[blockIdx.y];
-  const int lane = threadIdx.x & 63, ii = lane & 15;
-  const int r0 = k + NB + blockIdx.x * 64 + (threadIdx.x >> 6) * 16;
-  if (k >= jd.npad || r0 >= jd.npad) return;  // uniform per wavefront; no barrier below
+  const int t = threadIdx.x, lane = t & 63, ii = lane & 15, h = lane >> 4;
+  const int r0 = k + NB + blockIdx.x * 64 + (t >> 6) * 16;
+  if (k >= jd.npad || k + NB + (int)blockIdx.x * 64 >= jd.npad) return;  // uniform; npad is a multiple of 64
   T* A = work + jd.a_off;
   const int64_t ld = jd.npad;
-  StripMma<T, 4> d;
-  d.zero();
-  d.run([&](int i, int kk) { return A[(int64_t)(r0 + i) * ld + k + kk]; },
-        [&](int kk, int c) {
-          T u = A[(int64_t)(k + kk) * ld + k + c];
-          if (kk > c) u = T{0, 0};
-          return u;
-        },
-        lane);
+  typedef typename LdsOf<T>::type S;
+  constexpr bool F32 = sizeof(T) == sizeof(float2);
+  // the k of step q of a 16-column block in lane quarter h: 64 bytes of a row per load
+  auto kof = [](int q, int hh) { return F32 ? 8 * (q >> 1) + 2 * hh + (q & 1) : 4 * q + hh; };
+  __shared__ S s_U[NB][NB + (F32 ? 8 : 2)];
+  constexpr int P = 16 / (int)sizeof(T), PR = NB / P;  // elements per 16-byte piece, pieces per row
+  T a[4][4];
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[kb][q] = A[(int64_t)(r0 + ii) * ld + k + kb * 16 + kof(q, h)];
+#pragma unroll
+  for (int u = 0; u < NB * PR / 256; ++u) {
+    const int idx = t + 256 * u, row = idx / PR, c = idx % PR * P;
+    T v[P];
+    *(float4*)v = *(const float4*)(A + (int64_t)(k + row) * ld + k + c);
+#pragma unroll
+    for (int e = 0; e < P; ++e) st2(&s_U[row][c + e], row <= c + e ? wide(v[e]) : double2{0, 0});
+  }
+  __syncthreads();
+  StripMma<T, 1, 16> d[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) d[cb].zero();
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+    for (int cb = kb; cb < 4; ++cb)  // U11^-1 is zero below its diagonal
+      d[cb].run_regs(a[kb], [&](int kk, int c) { return s_U[kb * 16 + kof(kk >> 2, kk & 3)][cb * 16 + c]; }, lane);
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) st2(A + (int64_t)(r0 + d.row(r, lane)) * ld + k + cb * 16 + ii, d.value(cb, r));
+    for (int r = 0; r < 4; ++r) st2(A + (int64_t)(r0 + d[cb].row(r, lane)) * ld + k + cb * 16 + ii, d[cb].value(0, r));
 }
 
 // ------------------------------------------------------------------------------------
