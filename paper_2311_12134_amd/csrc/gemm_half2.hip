@@ -168,6 +168,11 @@ __global__ __launch_bounds__(256) void split_half2_kernel(const JobDesc* jobs, i
 // block ahead of the stores (7.3 ms with one load and store at a time); staging through
 // registers instead of straight to LDS 7.0, 128 x 64 tiles at three workgroups per compute
 // unit 8.4, touching the tile's lines early to bring them into L2 7.5.
+// LOWER: only the tiles on and below the diagonal (rows and columns begin together), numbered row by
+// row; of a tile on the diagonal the 64 x 64 block above it is left as it is.  125 systems of npad
+// 1472, K = 256: 655 us a launch and 334 for the pairs on average, where two launches of K = 128 took
+// 683 each on the FP32 matrix cores.
+template <bool LOWER>
 __global__ __launch_bounds__(256, 2) void gemm_half2_kernel(const JobDesc* jobs, int tiles_x, int tiles_y, int rows,
                                                             int cols, int kd, int r_begin, int c_begin, int c_end,
                                                             const char* scratch, float2* work) {
@@ -177,10 +182,16 @@ __global__ __launch_bounds__(256, 2) void gemm_half2_kernel(const JobDesc* jobs,
     const int N = gridDim.x, q = N >> 3, r = N & 7, x = T & 7;
     T = x * q + min(x, r) + (T >> 3);
   }
-  const int tpj = tiles_x * tiles_y;
+  const int tpj = LOWER ? tiles_y * (tiles_y + 1) / 2 : tiles_x * tiles_y;
   const int job = T / tpj;
   int tx, ty;
-  {
+  if constexpr (LOWER) {
+    const int u = T - job * tpj;
+    ty = (int)((sqrtf(8.f * u + 1.f) - 1.f) * 0.5f);
+    while (ty * (ty + 1) / 2 > u) --ty;
+    while ((ty + 1) * (ty + 2) / 2 <= u) ++ty;
+    tx = u - ty * (ty + 1) / 2;
+  } else {
     const int u = T - job * tpj;
     const int band = u / (BAND * tiles_x), rem = u - band * BAND * tiles_x;
     const int h = min(BAND, tiles_y - band * BAND);
@@ -241,6 +252,7 @@ __global__ __launch_bounds__(256, 2) void gemm_half2_kernel(const JobDesc* jobs,
            (lane & 31);
   };
   auto inside = [&](int b) {  // uniform
+    if (LOWER && row0 == col0 && wm < wn) return false;
     return row0 + wm * 64 + (b >> 1) * 32 < npad && col0 + wn * 64 + (b & 1) * 32 < cmax;
   };
   auto load_c = [&](int b) {
@@ -334,7 +346,7 @@ size_t half2_scratch_bytes(int njobs, int npad_max, int group) {
 
 // The scratch must hold at least one job (half2_job_bytes); kd a multiple of 64 up to 256.
 void launch_gemm_half2(const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd, int r_begin, int c_begin,
-                       int c_end, float2* work, const Half2Scratch& scratch, hipStream_t s) {
+                       int c_end, float2* work, const Half2Scratch& scratch, hipStream_t s, bool lower) {
   const Half2Layout lay = half2_layout(rows, cols, kd);
   const int group = (int)std::min<int64_t>(njobs, (int64_t)scratch.bytes / lay.bytes);
   const int tx = (cols + 127) / 128, ty = (rows + 127) / 128;
@@ -343,8 +355,12 @@ void launch_gemm_half2(const JobDesc* jobs, int njobs, int rows, int cols, int k
     half2_scale_kernel<<<dim3(kd / 4, nj), 256, 0, s>>>(jobs + j, rows, cols, k, kd, work, (char*)scratch.p);
     split_half2_kernel<<<dim3(lay.rb + lay.cb, nj), 256, 0, s>>>(jobs + j, rows, cols, k, kd, r_begin, c_begin, c_end,
                                                                  work, (char*)scratch.p);
-    gemm_half2_kernel<<<(unsigned)((int64_t)tx * ty * nj), 256, 0, s>>>(jobs + j, tx, ty, rows, cols, kd, r_begin,
-                                                                        c_begin, c_end, (const char*)scratch.p, work);
+    if (lower)
+      gemm_half2_kernel<true><<<(unsigned)((int64_t)ty * (ty + 1) / 2 * nj), 256, 0, s>>>(
+          jobs + j, tx, ty, rows, cols, kd, r_begin, c_begin, c_end, (const char*)scratch.p, work);
+    else
+      gemm_half2_kernel<false><<<(unsigned)((int64_t)tx * ty * nj), 256, 0, s>>>(
+          jobs + j, tx, ty, rows, cols, kd, r_begin, c_begin, c_end, (const char*)scratch.p, work);
   }
 }
 

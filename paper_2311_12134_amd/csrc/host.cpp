@@ -707,8 +707,9 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
     rc = ensure_dev(ctx->ldlt, ldlt_scratch_bytes(nj), s);
     if (rc) return rc;
   }
-  const Half2Scratch half2 =
-      precision == LSMS_SPLIT && !sym ? half2_scratch(ctx, nj, npad_max, tiling, s) : Half2Scratch{};
+  Tiling update = tiling;
+  if (sym) update.group = LDLT_GROUP;
+  const Half2Scratch half2 = precision == LSMS_SPLIT ? half2_scratch(ctx, nj, npad_max, update, s) : Half2Scratch{};
   const SideStream* side = nullptr;
   const bool capture = ctx->graphs && !prof;
   if (!capture) {  // captured graphs keep the single-stream order
@@ -721,7 +722,7 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
       lu_solve_f64(jd, nj, npad_max, (const double2*)abuf, piv, xbuf, 0, 16, 0, tiling.group, q);
     } else {
       if (sym)
-        ldlt_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, variant, NB, ctx->ldlt.p);
+        ldlt_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, half2, NB, ctx->ldlt.p);
       else
         lu_factor_f32(jd, nj, npad_max, (float2*)abuf, piv, jinfo, q, pr, tiling, ts, half2, side);
       // the first solve in FP32 on a rounded copy of the right-hand side (refined below)

@@ -1476,7 +1476,7 @@ size_t ldlt_scratch_bytes(int njobs) {
 }
 
 void ldlt_factor_f32(const JobDesc* jobs, int njobs, int npad_max, float2* work, int32_t* piv, int32_t* info,
-                     hipStream_t s, GemmProfiler* prof, int gemm_variant, int tall_rows, void* scratch) {
+                     hipStream_t s, GemmProfiler* prof, const Half2Scratch& half2, int tall_rows, void* scratch) {
   JobDesc* sub = (JobDesc*)scratch;
   int32_t* spiv = (int32_t*)((char*)scratch + (njobs * sizeof(JobDesc) + 255) / 256 * 256);
   int32_t* sinfo = spiv + (int64_t)njobs * piv_ints(NB);
@@ -1502,10 +1502,12 @@ void ldlt_factor_f32(const JobDesc* jobs, int njobs, int npad_max, float2* work,
     const int rows = npad_max - rb;
     if (rows <= 0) return;
     if (prof) prof->before(s);
-    if (lower)
+    if (lower && half2.p && half2_update(rows, kd))
+      launch_gemm_half2(jobs, njobs, rows, rows, k, kd, rb, rb, 0, work, half2, s, true);
+    else if (lower)
       launch_gemm_f32_lower(jobs, njobs, rows, k, kd, rb, work, s);
     else
-      launch_gemm_f32(0, jobs, njobs, rows, std::min(c_end, npad_max) - rb, k, kd, rb, rb, c_end, work, s);
+      launch_gemm_f32(7, jobs, njobs, rows, std::min(c_end, npad_max) - rb, k, kd, rb, rb, c_end, work, s);
     if (prof) {
       // algorithmic work: the lower triangle (with diagonal) of each job's unpadded block
       double f = 0.0, b = 0.0;
@@ -1520,16 +1522,13 @@ void ldlt_factor_f32(const JobDesc* jobs, int njobs, int npad_max, float2* work,
       prof->after(s, f, b, lower ? 1 : 0);
     }
   };
-  (void)gemm_variant;
-  for (int k = 0; k < npad_max; k += 2 * NB) {
-    panel(k);
-    const int rest = npad_max - k - NB;
-    if (rest <= 0) break;
-    timed(k, NB, k + NB, false, k + 2 * NB);  // the second panel's columns
-    panel(k + NB);
-    const int rest2 = npad_max - k - 2 * NB;
-    if (rest2 <= 0) break;
-    timed(k, 2 * NB, k + 2 * NB, true, 0);
+  constexpr int GW = LDLT_GROUP * NB;
+  for (int k = 0; k < npad_max; k += GW) {
+    for (int kj = k; kj < std::min(k + GW, npad_max); kj += NB) {
+      if (kj > k) timed(k, kj - k, kj, false, kj + NB);  // the panel's columns
+      panel(kj);
+    }
+    if (npad_max > k + GW) timed(k, GW, k + GW, true, 0);
   }
 }
 

@@ -82,3 +82,27 @@ def test_zero_blocks_and_non_finite_rows(ctx):
     assert np.array_equal(x[0], b)
     assert np.array_equal(np.isnan(x[1]), np.isnan(x32[1])) and np.isnan(x[1]).any()
     assert np.abs(good @ x[2] - b).max() <= 1e-4 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("radius", [1.7, 2.1, 2.2])
+def test_symmetric_factorization(radius):
+    """The lower-triangle form of the update at edges of its 128-row tiles: LIZ of a finite bcc cluster, so the
+    systems of one batch differ in size (up to 832, 1088 and 1472 rows), against the FP64 LU.  Refined to a backward
+    error of 1e-14, the solutions differ by that times the condition (below 1e3 here)."""
+    import paper_2311_12134_amd as P
+    a = 5.7
+    grid = np.array([(i, j, k) for i in range(5) for j in range(5) for k in range(5)], dtype=np.float64)
+    pos = np.concatenate([grid, grid + 0.5]) * a
+    inner = [62, 187, 0, 31, 124, 93, 186]
+    ctx = P.Context(0)
+    liz = P.build_liz(pos, None, radius * a, centres=inner)
+    assert len(set(np.diff(liz.ptr)[inner])) > 2
+    atom, dpos = liz.to_device(ctx.device)
+    phase = torch.from_numpy(np.random.default_rng(4).uniform(-0.5, 0.5, (len(pos), 4))).cuda()
+    want = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.01, precision="fp64")[:2]
+    ctx.set_symmetric(True)
+    tp, tm, info, berr = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.01, precision="split")
+    assert int(info.abs().max()) == 0 and float(berr.min()) >= 0  # no system fell back to the FP64 LU
+    for got, ref in zip((tp, tm), want):
+        assert float((got - ref).norm() / ref.norm()) <= 1e-11
+    ctx.close()
