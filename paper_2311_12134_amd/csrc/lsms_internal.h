@@ -84,10 +84,15 @@ constexpr int NRHS_MAX = 32;  // columns of the solution block (16 forward, 32 a
 // Split mode keeps, per pair of LIZ members a < b, the FP64 Gaunt contraction
 // v^{ab}_{LL'} = sum_{L''} C_{L L' L''} (-4 pi i kappa) i^{l''} h_{l''}(kappa |R|) Y_{L''}(R^), R = p_a - p_b,
 // so that g^{ab} = i^l v^{ab} i^{-l'}.  v is symmetric in (L, L') and is stored as its upper
-// triangle, row by row: VBLOCK complex entries per pair, the pair numbered like the upper
+// triangle: VBLOCK complex entries per pair, the pair numbered like the upper
 // triangle of the member grid (pair_index).  For the reversed pair v^{ba} = (-1)^{l + l'} v^{ab}.
+// Rows L < 8 and 15 - L share a run of 17 entries, the first from its last column down, the second
+// up to its last: a wavefront that takes column L' (or row L') of all sixteen L from LDS meets
+// every group of four banks at most twice.
 constexpr int VBLOCK = NL * (NL + 1) / 2;
-__host__ __device__ inline int vblock_index(int L, int Lp) { return L * NL - L * (L - 1) / 2 + (Lp - L); }  // L <= Lp
+__host__ __device__ inline int vblock_index(int L, int Lp) {  // L <= Lp
+  return L < NL / 2 ? (NL + 1) * L + NL - 1 - Lp : (NL + 1) * (NL - 1 - L) + 1 + Lp;
+}
 // pair a <= b of an nb x nb grid, numbered row by row
 __host__ __device__ inline int64_t pair_index(int a, int b, int nb) {
   return (int64_t)a * nb - (int64_t)a * (a - 1) / 2 + (b - a);

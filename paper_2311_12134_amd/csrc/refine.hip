@@ -52,24 +52,27 @@ __global__ void rotate_x_kernel(const JobDesc* jobs, const int32_t* liz_atom, co
 }
 
 // r = B - M X for the 16 rows of one member per wavefront (four per workgroup): per member
-// b != a the 16 x 16 block v^{ab} is read from the packed table straight into the FP64 MFMA
-// operand layout (lane l, step s: entry (l % 16, 4 s + l / 16), the table's upper triangle by
-// symmetry; reversed pairs take the sign (-1)^{l + l'}), X'_b from the rotated rows, and
-// v X' accumulates with three real products per complex product (Ar Br, Ai Bi,
-// (Ar + Ai)(Br + Bi)); table blocks load RDEPTH members ahead, X' one member ahead, while
+// b != a the packed 16 x 16 block v^{ab} is read as it lies, into LDS, and taken from there in the
+// FP64 MFMA operand layout (lane l, step s: entry (l % 16, 4 s + l / 16), the table's upper triangle by
+// symmetry; reversed pairs take the sign (-1)^{l + l'}), X'_b passes through LDS for all four of the
+// workgroup's members, and v X' accumulates with three real products per complex product; table
+// blocks load RDEPTH members ahead, X' a chunk of RCHUNK members ahead, while
 // the current products run.  Reads 2176 bytes of table per block instead of the 4 KB of a
-// stored FP64 block of M; these reads do not bound the kernel (loading further ahead, or
-// keeping the loads ahead of the products, leaves its time unchanged).
-// Each pair's block has two readers (rows a and b): the members are visited in the cyclic
-// order a + 1, a - 1, a + 2, a - 2, ... (mod nl), so both readers of pair (a, a + t) reach it
-// within one block of each other, and a job's workgroups are dealt to one XCD (workgroups
+// stored FP64 block of M.  The FP64 matrix cores bound it (busy 70 % of its clocks; a
+// block's products take a SIMD 768), and beside them the table, at 4.4 TB/s with both readings of every
+// block.  1280 systems of n = 2160: 13.6 -> 11.9 ms (first pass 15.7 -> 14.4), against every wavefront
+// reading table and X' for itself through the vector cache in operand layout; with only X' through
+// LDS 12.1 (14.7), n = 15,440 4.77 against 4.52.
+// Each pair's block has two readers (rows a and b): a workgroup visits the members in the cyclic
+// order a, a + 1, a - 1, a + 2, a - 2, ... (mod nl) from its first one, so both readers of a pair reach it
+// within a few blocks of each other, and a job's workgroups are dealt to one XCD (workgroups
 // go to the eight XCDs round-robin), so that the second read may find the block in that
 // XCD's L2 (the fetch counters show it mostly does not; the order costs nothing).
 // MNORM: also ||M||_inf (first pass of a refinement): per row 1 + |d_l| sum |v e|, the moduli
 // in FP32 (a relative error of about 1e-7 in a norm that only scales the backward error),
 // summed in FP64.
-constexpr int RDEPTH = 2;
-static_assert(RDEPTH % 2 == 0, "the X' register sets alternate by block parity across the unrolled steps");
+constexpr int RDEPTH = 2, RCHUNK = 4;
+static_assert(RCHUNK % RDEPTH == 0, "a member's table registers are chosen by its place in the unrolled chunk");
 
 template <bool MNORM, bool SYM>
 __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(const JobDesc* jobs, const double2* vtab,
@@ -97,43 +100,66 @@ __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(con
   const int eoff = jd.energy * 4;
   d4 t1 = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
   double rowabs = 0.0;
-  if (a < nl) {  // uniform per wavefront
+  {
     const int i = lane & 15;
     int toff[4];
-    double sg[4];
+    unsigned odd[4];  // the sign bit where l + l' is odd
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int k = 4 * s + (lane >> 4);
       toff[s] = i <= k ? vblock_index(i, k) : vblock_index(k, i);
-      sg[s] = ((lch(i) + lch(k)) & 1) ? -1.0 : 1.0;
+      odd[s] = ((lch(i) + lch(k)) & 1) ? 0x80000000u : 0u;
     }
-    const int xo = (lane >> 4) * NRHS_MAX + i;  // X' entry (row b NL + lane / 16 + 4 s)
-    // block k of the cyclic order: member a + (k / 2 + 1) for even k, a - (k / 2 + 1) for odd k
+    // block k of the workgroup's cyclic order from its first member a0
+    const int a0 = row0 / NL;
     auto member = [&](int k) {
-      const int d = (k >> 1) + 1;
-      return (k & 1) ? (a - d + nl) % nl : (a + d) % nl;
+      const int d = (k + 1) >> 1, b = (k & 1) ? a0 + d : a0 - d;
+      return b >= nl ? b - nl : b < 0 ? b + nl : b;
     };
-    const int nblk = nl - 1;
-    auto load_v = [&](int k, double2* av) {
-      if (k < nblk) {  // uniform
+    // table blocks pass through LDS too, each wavefront's by itself: read as they lie (three
+    // loads), taken in operand layout
+    typedef double dv2 __attribute__((ext_vector_type(2)));
+    __shared__ double2 s_v[4][2][VBLOCK];
+    dv2 av[RDEPTH][3];
+    auto mine = [&](int k) { return k < nl && a < nl && member(k) != a; };  // uniform per wavefront
+    auto load_v = [&](int k, dv2* v) {
+      if (mine(k)) {
         const int b = member(k);
-        const double2* blk = V + pair_index(min(a, b), max(a, b), nb) * VBLOCK;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) av[s] = blk[toff[s]];
+        const dv2* blk = (const dv2*)(V + pair_index(min(a, b), max(a, b), nb) * VBLOCK);
+        v[0] = blk[lane];
+        v[1] = blk[64 + lane];
+        if (lane < VBLOCK - 128) v[2] = blk[128 + lane];
       }
     };
-    auto load_x = [&](int k, double2* xv) {
-      if (k < nblk) {  // uniform
-        const int b = member(k);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) xv[s] = Xr[(int64_t)b * NL * NRHS_MAX + xo + 4 * s * NRHS_MAX];
-      }
+    auto store_v = [&](int buf, const dv2* v) {
+      dv2* d = (dv2*)s_v[wave][buf];
+      d[lane] = v[0];
+      d[64 + lane] = v[1];
+      if (lane < VBLOCK - 128) d[128 + lane] = v[2];
     };
-    auto mul = [&](int k, const double2* av, const double2* xv) {
-      const int b = member(k);
-      double2 A[4];
+    __shared__ double2 s_x[2][RCHUNK][NL * NL];  // X' of a chunk's members, as the rows lie
+    dv2 xs[RCHUNK];
+    auto load_x = [&](int k0) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) A[s] = b < a ? make_double2(sg[s] * av[s].x, sg[s] * av[s].y) : av[s];
+      for (int u = 0; u < RCHUNK; ++u)
+        xs[u] = *(const dv2*)(Xr + ((int64_t)member(min(k0 + u, nl - 1)) * NL + (t >> 4)) * NRHS_MAX + (t & 15));
+    };
+    auto store_x = [&](int buf) {
+#pragma unroll
+      for (int u = 0; u < RCHUNK; ++u) *(dv2*)&s_x[buf][u][t] = xs[u];
+    };
+    auto flip = [](double x, unsigned bit) {
+      return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, x) ^ ((unsigned long long)bit << 32));
+    };
+    auto mul = [&](int b, const double2* vb, const double2* xb) {
+      double2 A[4], xv[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {  // X' entry (row 4 s + lane / 16, column i)
+        xv[s] = xb[64 * s + lane];
+        const unsigned bit = b < a ? odd[s] : 0u;
+        const double2 v = vb[toff[s]];
+        A[s] = make_double2(flip(v.x, bit), flip(v.y, bit));
+      }
       if (MNORM) {
         double2 eb[4];
         if (SYM) {
@@ -155,21 +181,25 @@ __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(con
         t3 = __builtin_amdgcn_mfma_f64_16x16x4f64(A[s].x + A[s].y, xv[s].x + xv[s].y, t3, 0, 0, 0);
       }
     };
-    // table blocks load RDEPTH blocks ahead (they come from HBM), X' one block ahead (it stays
-    // in L2); static register sets through unrolling
-    double2 av[RDEPTH][4], xv[2][4];
 #pragma unroll
     for (int u = 0; u < RDEPTH; ++u) load_v(u, av[u]);
-    load_x(0, xv[0]);
-    for (int k = 0; k < nblk; k += RDEPTH) {
+    load_x(0);
+    store_x(0);
+    store_v(0, av[0]);
+    lds_barrier();
+    for (int k = 0; k < nl; k += RCHUNK) {
+      const int cur = (k / RCHUNK) & 1;
+      load_x(k + RCHUNK);
 #pragma unroll
-      for (int u = 0; u < RDEPTH; ++u) {
-        if (k + u < nblk) {  // uniform
-          load_x(k + u + 1, xv[(u + 1) & 1]);
-          mul(k + u, av[u], xv[u & 1]);
-          load_v(k + u + RDEPTH, av[u]);
-        }
+      for (int u = 0; u < RCHUNK; ++u) {  // block k + u: in s_v[u & 1]; k + u + 1: in av[(u + 1) % RDEPTH]
+        load_v(k + u + RDEPTH, av[u % RDEPTH]);
+        if (mine(k + u)) mul(member(k + u), s_v[wave][u & 1], s_x[cur][u]);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        store_v((u + 1) & 1, av[(u + 1) % RDEPTH]);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       }
+      store_x(cur ^ 1);  // its last readers passed the previous barrier
+      lds_barrier();
     }
   }
   // ||M||_inf over the member's rows: lanes l, l + 16, l + 32, l + 48 hold parts of row l % 16
