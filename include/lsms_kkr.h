@@ -331,7 +331,7 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
 /*
  * knob LSMS_TUNE_TSLU_CHUNK (a multiple of 64 in [64, 2048], default 2048): a panel of the
  * LU with more than 2 C rows is not factored by one workgroup but by tournament pivoting
- * (communication-avoiding LU): chunks of C rows each nominate 64 rows by partial
+ * (communication-avoiding LU): chunks of C rows (at most 1536) each nominate 64 rows by partial
  * pivoting, one more partial-pivoting factorization of the nominees picks the panel's 64
  * pivot rows, and the rows below are L21 = A21 U11^-1.  C is raised where needed so that
  * the nominees fit one 4096-row block.  Smaller C exercises the path on smaller systems;

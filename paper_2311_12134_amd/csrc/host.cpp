@@ -202,15 +202,16 @@ static int ensure_dev(DevBuf& b, size_t bytes, hipStream_t s) {
 }
 
 // Scratch for the tournament-pivoting panels of a batch of njobs systems of padded size
-// npad_max (none below 2 chunks).  The chunk is raised if needed so that the candidates
+// npad_max (none up to twice the knob's rows).  The chunk is raised if needed so that the candidates
 // of all chunks (NB rows each) form a block of at most 4096 rows.
 static int tall_scratch(lsms_ctx* ctx, int njobs, int npad_max, TallScratch* ts, hipStream_t s) {
   const int min_chunk = ((npad_max + 64 * NB - 1) / (64 * NB)) * NB;
-  ts->chunk = std::max(ctx->tslu_chunk, min_chunk);
+  ts->chunk = std::max(std::min(ctx->tslu_chunk, TALL_CHUNK), min_chunk);
+  ts->above = 2 * std::max(ctx->tslu_chunk, min_chunk);
   ts->njobs = njobs;
   ts->npad_max = npad_max;
   ts->base = nullptr;
-  const size_t bytes = tall_scratch_bytes(njobs, npad_max, ts->chunk);
+  const size_t bytes = tall_scratch_bytes(njobs, npad_max, ts->chunk, ts->above);
   if (bytes == 0) return LSMS_OK;
   int rc = ensure_dev(ctx->tall, bytes, s);
   if (rc) return rc;
@@ -739,7 +740,7 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
   const std::vector<intptr_t> key = {precision, nj, npad_max, variant, tiling.narrow, tiling.panel_small_rows,
                                      tiling.group,
                                      (intptr_t)jd, (intptr_t)abuf,
-                                     (intptr_t)piv, (intptr_t)jinfo, (intptr_t)xbuf, ts.chunk,
+                                     (intptr_t)piv, (intptr_t)jinfo, (intptr_t)xbuf, ts.chunk, ts.above,
                                      (intptr_t)ts.base, sym ? 1 : 0, (intptr_t)ctx->ldlt.p,
                                      (intptr_t)half2.p, (intptr_t)half2.bytes};
   auto it = ctx->graph_cache.find(key);

@@ -228,14 +228,20 @@ void launch_gemm_f32_lower(const JobDesc* jobs, int njobs, int rows, int k, int 
                            hipStream_t s);
 
 // Blocked LU with partial pivoting of every job's working matrix.
-// Panels taller than 2 * chunk rows are factored with tournament pivoting (lu.hip);
+// Panels of more than `above` rows are factored with tournament pivoting (lu.hip);
 // they need device scratch laid out for the wave's job count and padded size.
+// Chunks of 1536 rows where the threshold would allow 2048: more workgroups in the first round, on
+// panels that a compute unit factors in 180 us instead of 290 (three row slots a thread, not four),
+// against a block of nominees a third higher.  n = 15,440: 8 systems 467 -> 459 ms a step, 52 systems 2.286 ->
+// 2.274 s; 1024 rows 456 ms and 2.327 s.
+constexpr int TALL_CHUNK = 1536;
 struct TallScratch {
-  int chunk = 0;         // rows per tournament chunk (64 .. 2048, a multiple of 64)
-  void* base = nullptr;  // tall_scratch_bytes(njobs, npad_max, chunk) bytes, or nullptr if none needed
+  int chunk = 0;         // rows per tournament chunk (a multiple of 64)
+  int above = 0;         // rows of the tallest panel of one workgroup
+  void* base = nullptr;  // tall_scratch_bytes(..) bytes, or nullptr if none needed
   int njobs = 0, npad_max = 0;
 };
-size_t tall_scratch_bytes(int njobs, int npad_max, int chunk);
+size_t tall_scratch_bytes(int njobs, int npad_max, int chunk, int above);
 
 // Optional second stream for the look-ahead panel (lu.hip); nullptr: one stream.
 struct SideStream {

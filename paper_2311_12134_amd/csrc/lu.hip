@@ -994,8 +994,8 @@ static TallLayout tall_layout(int njobs, int npad_max, int chunk) {
   return L;
 }
 
-size_t tall_scratch_bytes(int njobs, int npad_max, int chunk) {
-  if (chunk <= 0 || npad_max <= 2 * chunk) return 0;
+size_t tall_scratch_bytes(int njobs, int npad_max, int chunk, int above) {
+  if (chunk <= 0 || npad_max <= above) return 0;
   return (size_t)tall_layout(njobs, npad_max, chunk).total;
 }
 
@@ -1273,12 +1273,12 @@ void launch_panel_f32_variant(int variant, const JobDesc* jobs, int njobs, int r
 }
 
 // One panel (and the inverses of its diagonal triangles): the register-resident panel
-// kernel, or the tournament for panels taller than 2 chunk rows.
+// kernel, or the tournament for taller panels.
 template <typename T>
 static void panel_step(const JobDesc* jobs, int njobs, int npad_max, int k, int left, T* work, int32_t* piv,
                        int32_t* info, const TallScratch& ts, hipStream_t s, int small_rows) {
   const int rows = npad_max - k;
-  if (ts.chunk > 0 && rows > 2 * ts.chunk && ts.base) {
+  if (ts.chunk > 0 && rows > ts.above && ts.base) {
     const TallLayout L = tall_layout(ts.njobs, ts.npad_max, ts.chunk);
     char* b = (char*)ts.base;
     T* w1 = (T*)(b + L.w1);
