@@ -344,6 +344,8 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * rest of the current trailing update runs on the caller's stream; events order them and
  * the call's work is complete on the caller's stream when its last launch is.  Results
  * are bitwise those of 0.  Not used inside captured graphs (LSMS_TUNE_GRAPHS).
+ * With 0 the library does so by itself for split-mode waves of few systems with tournament
+ * panels (LSMS_TUNE_TSLU_CHUNK), unless kernel times are being recorded.
  */
 #define LSMS_TUNE_LOOKAHEAD 4
 /*

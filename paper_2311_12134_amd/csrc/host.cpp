@@ -684,12 +684,20 @@ void launch_fallback_status(int nf, const JobDesc* fjobs, const int32_t* finfo, 
 // caller's stream whenever the same shape and buffers come back.  Job descriptors, matrices
 // and right-hand sides are read from device memory at replay, after the caller's stream has
 // written them.
-static int side_stream(lsms_ctx* ctx, const SideStream** out) {
+// The look-ahead stream: where asked for, and for split-mode waves of few tall systems, whose tournament
+// panels leave most compute units idle (at most one workgroup each in their first round).  Results are bitwise
+// the same.  n = 15,440: 2 systems 208 -> 197 ms, 8 467 -> 450, 20 961 -> 950, with two thirds of the compute units
+// busy and more no gain; FP64 none (511 -> 514 ms); systems without tournament panels lose
+// as often as they gain (n = 2160: 2 systems 9.6 -> 9.9 ms, 12 11.3 -> 11.0, 96 27.6 -> 28.2).
+static int side_stream(lsms_ctx* ctx, int precision, int njobs, int npad_max, const TallScratch& ts, bool timed,
+                       const SideStream** out) {
   *out = nullptr;
-  if (!ctx->lookahead) return LSMS_OK;
-  if (!ctx->side.stream) {
-    HIP_TRY(hipStreamCreateWithFlags(&ctx->side.stream, hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&ctx->side.update_done, hipEventDisableTiming));
+  const bool few_tall = precision == LSMS_SPLIT && ts.base && !timed &&
+                        (int64_t)njobs * ((npad_max + ts.chunk - 1) / ts.chunk) <= ctx->cu_count;
+  if (!ctx->lookahead && !few_tall) return LSMS_OK;
+  if (!ctx->side.panel_done) {
+    if (!ctx->side.stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->side.stream, hipStreamNonBlocking));
+    if (!ctx->side.update_done) HIP_TRY(hipEventCreateWithFlags(&ctx->side.update_done, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&ctx->side.panel_done, hipEventDisableTiming));
   }
   *out = &ctx->side;
@@ -714,7 +722,7 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
   const SideStream* side = nullptr;
   const bool capture = ctx->graphs && !prof;
   if (!capture) {  // captured graphs keep the single-stream order
-    rc = side_stream(ctx, &side);
+    rc = side_stream(ctx, precision, nj, npad_max, ts, prof != nullptr, &side);
     if (rc) return rc;
   }
   auto issue = [&](hipStream_t q, GemmProfiler* pr) {

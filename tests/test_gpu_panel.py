@@ -65,3 +65,26 @@ def test_zero_pivot_is_reported_at_its_column(ctx, precision):
         rhs.append(np.ones((300, 1), dtype=np.complex128))
     _, info = _solve(ctx, mats, rhs, precision)
     assert list(info) == [c + 1 for c in cols]
+
+
+def test_few_tall_systems_look_ahead_bitwise(ctx):
+    """One LIZ of 259 members (n = 4160, tournament panels), where the next group's first panel runs on a stream of
+    its own, against graph replay, which keeps one stream."""
+    import paper_2311_12134_amd as P
+    cells, a = 8, 5.7
+    grid = np.array([(i, j, k) for i in range(cells) for j in range(cells) for k in range(cells)], dtype=np.float64)
+    pos = np.concatenate([grid, grid + 0.5]) * a
+    liz = P.build_liz(pos, np.eye(3) * cells * a, 3.001 * a, centres=[0])
+    assert liz.ptr[1] == 259
+    atom, dpos = liz.to_device(ctx.device)
+    phase = torch.from_numpy(np.random.default_rng(2).uniform(-0.6, 0.6, (len(pos), 4))).cuda()
+    got = []
+    for graphs in (False, True, True, False):
+        ctx.set_graphs(graphs)
+        tp, tm, info, _ = ctx.tau_solve(liz, atom, dpos, phase, 0.65, 0.005, precision="split")
+        torch.cuda.synchronize()
+        assert int(info.abs().max()) == 0
+        got.append((tp.clone(), tm.clone()))
+    ctx.set_graphs(False)
+    for tp, tm in got[1:]:
+        assert torch.equal(tp, got[0][0]) and torch.equal(tm, got[0][1])
