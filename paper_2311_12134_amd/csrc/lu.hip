@@ -146,49 +146,6 @@ __device__ inline void wave_sync() {
 }
 
 __device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl(v.x, src), __shfl(v.y, src)); }
-// The NB interchanges of a panel starting at row k (pivall[q]: the row exchanged with
-// k + q at step q) as one permutation of at most 2 NB rows, written to lst: entries
-// 0..NB-1 are the positions k..k+NB-1, further entries the pivot rows below the panel;
-// org[e] is the original row that ends up at position pos[e].  Executed by one wavefront;
-// returns the number of entries (the same in every lane).
-__device__ inline int write_perm_list(int k, const int* pivall, int* s_pos, int* s_org, int32_t* lst, int lane) {
-  for (int i = lane; i < NB; i += 64) {
-    s_pos[i] = k + i;
-    s_org[i] = k + i;
-  }
-  int cnt = NB;
-  for (int q = 0; q < NB; ++q) {
-    const int d = k + q, p = pivall[q];
-    if (p == d) continue;
-    int e;
-    if (p < k + NB) {
-      e = p - k;
-    } else {
-      const unsigned long long m = __ballot(NB + lane < cnt && s_pos[NB + lane] == p);
-      if (m) {
-        e = NB + __ffsll((long long)m) - 1;
-      } else {
-        e = cnt;
-        if (lane == 0) {
-          s_pos[cnt] = p;
-          s_org[cnt] = p;
-        }
-        ++cnt;
-      }
-    }
-    if (lane == 0) {
-      const int tmp = s_org[q];
-      s_org[q] = s_org[e];
-      s_org[e] = tmp;
-    }
-  }
-  if (lane == 0) lst[0] = cnt;
-  for (int i = lane; i < cnt; i += 64) {
-    lst[2 + i] = s_pos[i];
-    lst[2 + PERM_MAX + i] = s_org[i];
-  }
-  return cnt;
-}
 
 // nopiv: keep the diagonal row at every step (the symmetric factorization below); the
 // permutation list is then the identity.
@@ -1064,21 +1021,18 @@ __global__ __launch_bounds__(256) void tslu_gather_kernel(const JobDesc* jobs, i
   }
 }
 
-// Position (index into pos/row lists of cnt <= PERM_MAX entries) of value v, or -1.
-__device__ inline int find_entry(const int* arr, int cnt, int v, int lane) {
-  const unsigned long long m0 = __ballot(lane < cnt && arr[lane] == v);
-  if (m0) return __ffsll((long long)m0) - 1;
-  const unsigned long long m1 = __ballot(lane + 64 < cnt && arr[lane + 64] == v);
-  return m1 ? 64 + __ffsll((long long)m1) - 1 : -1;
-}
-
 // The tournament's winners become the panel's pivot rows: interchanges, permutation list,
 // L11\U11 from the final factorization, zero-pivot report.  One workgroup per job.
+// Bound by latency: the interchanges run through one wavefront's registers (lane i follows the row
+// that began at position k + i; the chosen rows' own places are known), and the rows move in rounds
+// of 128 (FP64 64) columns.  8 systems of n = 15,440: 66 -> 20 us, against interchanges and list
+// kept in LDS, one after the other, and rounds of 32 columns.  At most 64 registers a lane, so that the sixteen
+// wavefronts fit where one workgroup of the trailing update has left (on the look-ahead stream).
 template <typename T>
-__global__ __launch_bounds__(256) void tslu_apply_kernel(const JobDesc* jobs, int k, int left, int nc_max,
-                                                         const JobDesc* sub2, const int32_t* p2, const T* w2,
-                                                         const int32_t* g2, const int32_t* si2, T* work,
-                                                         int32_t* piv, int32_t* info) {
+__global__ __launch_bounds__(1024, 8) void tslu_apply_kernel(const JobDesc* jobs, int k, int left, int nc_max,
+                                                          const JobDesc* sub2, const int32_t* p2, const T* w2,
+                                                          const int32_t* g2, const int32_t* si2, T* work,
+                                                          int32_t* piv, int32_t* info) {
   const int j = blockIdx.x;
   const JobDesc jd = jobs[j];
   if (k >= jd.npad) return;  // uniform
@@ -1086,68 +1040,69 @@ __global__ __launch_bounds__(256) void tslu_apply_kernel(const JobDesc* jobs, in
   T* A = work + jd.a_off;
   const int64_t ld = jd.npad;
   int32_t* ip = piv + jd.piv_off;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  __shared__ int s_sel[NB], s_pivall[NB];
-  __shared__ int s_mpos[PERM_MAX], s_mrow[PERM_MAX];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   __shared__ int s_pos[PERM_MAX], s_org[PERM_MAX], s_cnt;
-  __shared__ T s_held[PERM_MAX][33];
   const int32_t* lst2 = p2 + rd.piv_off + perm_off(rd.npad, 0);
-  if (t < NB) s_sel[t] = g2[(int64_t)j * nc_max * NB + lst2[2 + PERM_MAX + t]];
-  __syncthreads();
   if (wave == 0) {
-    // Interchanges that bring s_sel[q] to position k + q for q = 0, 1, ... in turn, as
-    // partial pivoting records them: (s_mpos[e], s_mrow[e]) lists the positions whose row
-    // has changed and the row each now holds (at most 2 NB entries).
-    int cnt = 0;
+    // Interchanges that bring the chosen row of lane q to position k + q for q = 0, 1, ... in turn, as
+    // partial pivoting records them.  Rows from below the panel stay where they are until chosen.
+    const int sel = g2[(int64_t)j * nc_max * NB + lst2[2 + PERM_MAX + lane]];
+    int now = k + lane, pivot = 0;  // where the row that began at k + lane is
+#pragma unroll
     for (int q = 0; q < NB; ++q) {
-      const int row = s_sel[q], d = k + q;
-      const int er = find_entry(s_mrow, cnt, row, lane);
-      const int p = er >= 0 ? s_mpos[er] : row;  // where that row is now
-      if (lane == 0) s_pivall[q] = p;
-      if (p != d) {
-        const int ed = find_entry(s_mpos, cnt, d, lane);
-        const int at_d = ed >= 0 ? s_mrow[ed] : d;
-        if (lane == 0) {
-          if (ed >= 0) {
-            s_mrow[ed] = row;
-          } else {
-            s_mpos[cnt] = d;
-            s_mrow[cnt] = row;
-          }
-          const int e2 = ed >= 0 ? cnt : cnt + 1;
-          if (er >= 0) {
-            s_mrow[er] = at_d;
-          } else {
-            s_mpos[e2] = p;
-            s_mrow[e2] = at_d;
-          }
-        }
-        cnt += (ed >= 0 ? 0 : 1) + (er >= 0 ? 0 : 1);
-      }
+      const int row = __builtin_amdgcn_readlane(sel, q), d = k + q, top = row - k;
+      const int p = top < NB ? __builtin_amdgcn_readlane(now, top & (NB - 1)) : row;
+      now = lane == top ? d : now == d ? p : now;
+      if (lane == q) pivot = p;
     }
-    for (int q = lane; q < NB; q += 64) ip[k + q] = s_pivall[q];
-    const int c = write_perm_list(k, s_pivall, s_pos, s_org, ip + perm_off(jd.npad, k), lane);
-    if (lane == 0) s_cnt = c;  // (pos, org) stay in LDS for the other wavefronts
+    ip[k + lane] = pivot;
+    // position k + i ends with row sel of lane i; the panel's rows that left it follow
+    const bool out = now >= k + NB;
+    const unsigned long long m = __ballot(out);
+    const int cnt = NB + __popcll(m), slot = NB + __popcll(m & ((1ull << lane) - 1));
+    s_pos[lane] = k + lane;
+    s_org[lane] = sel;
+    if (out) {
+      s_pos[slot] = now;
+      s_org[slot] = k + lane;
+    }
+    if (lane == 0) s_cnt = cnt;
+    int32_t* lst = ip + perm_off(jd.npad, k);
+    if (lane == 0) lst[0] = cnt;
+    lst[2 + lane] = k + lane;
+    lst[2 + PERM_MAX + lane] = sel;
+    if (out) {
+      lst[2 + slot] = now;
+      lst[2 + PERM_MAX + slot] = k + lane;
+    }
   }
   __syncthreads();
-  // the permutation on the panel's columns and the `left` columns before them
-  const int cnt = s_cnt;
-  const int ncols = left + NB;
-  for (int c0 = 0; c0 < ncols; c0 += 32) {
-    for (int idx = t; idx < cnt * 32; idx += 256) {
-      const int e = idx >> 5, cc = idx & 31;
-      if (c0 + cc < ncols) s_held[e][cc] = A[(int64_t)s_org[e] * ld + (k - left) + c0 + cc];
+  // the permutation on the panel's columns and the `left` columns before them, a wavefront per 64
+  // entries of a row, every source read before any destination is written
+  constexpr int CB = sizeof(T) == sizeof(float2) ? 2 : 1;  // 64-column blocks per round
+  constexpr int HELD = PERM_MAX * CB / 16;
+  const int cnt = s_cnt, blocks = left / NB + 1;
+  for (int b0 = 0; b0 < blocks; b0 += CB) {
+    const int nb = min(CB, blocks - b0);  // uniform
+    T* P = A + (k - left) + b0 * NB + lane;
+    typedef decltype(T::x) V2 __attribute__((ext_vector_type(2)));
+    V2 held[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const int id = wave + 16 * u, e = id / nb;
+      if (e < cnt) held[u] = *(const V2*)(P + (int64_t)s_org[e] * ld + (id - e * nb) * NB);
     }
     __syncthreads();
-    for (int idx = t; idx < cnt * 32; idx += 256) {
-      const int e = idx >> 5, cc = idx & 31;
-      if (c0 + cc < ncols) A[(int64_t)s_pos[e] * ld + (k - left) + c0 + cc] = s_held[e][cc];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const int id = wave + 16 * u, e = id / nb;
+      if (e < cnt) *(V2*)(P + (int64_t)s_pos[e] * ld + (id - e * nb) * NB) = held[u];
     }
-    __syncthreads();
   }
+  __syncthreads();
   // L11\U11 of the chosen rows, as the final factorization left them
   const T* top = w2 + (int64_t)j * nc_max * NB * NB;
-  for (int idx = t; idx < NB * NB; idx += 256) {
+  for (int idx = t; idx < NB * NB; idx += 1024) {
     const int q = idx / NB, pp = idx - q * NB;
     A[(int64_t)(k + q) * ld + k + pp] = top[(int64_t)q * NB + pp];
   }
@@ -1298,7 +1253,7 @@ static void panel_step(const JobDesc* jobs, int njobs, int npad_max, int k, int 
     launch_panel<T>(sub1, njobs * nc_max, 0, 0, ts.chunk, w1, p1, si1, s);
     tslu_gather_kernel<T><<<dim3(nc_max, njobs), 256, 0, s>>>(jobs, k, ts.chunk, nc_max, sub1, p1, work, w2, g2);
     launch_panel<T>(sub2, njobs, 0, 0, ((rows + ts.chunk - 1) / ts.chunk) * NB, w2, p2, si2, s);
-    tslu_apply_kernel<T><<<njobs, 256, 0, s>>>(jobs, k, left, nc_max, sub2, p2, w2, g2, si2, work, piv, info);
+    tslu_apply_kernel<T><<<njobs, 1024, 0, s>>>(jobs, k, left, nc_max, sub2, p2, w2, g2, si2, work, piv, info);
     launch_linv<T>(jobs, njobs, k, work, s);
     if (rows > NB) tslu_l21_kernel<T><<<dim3((rows - NB + 63) / 64, njobs), 256, 0, s>>>(jobs, k, work);
     return;
