@@ -173,12 +173,22 @@ static void launch_tiled64(const JobDesc* jobs, int njobs, int rows, int cols, i
 
 int gemm_f64_variants() { return 6; }
 
+constexpr int64_t FEW_TILES = 4 * 256;
+
 // 0: the single-buffered 64 x 64 kernel (gemm.hip); 1: 64 x 64, two LDS stages of K = 8, XCD
 // order; 2: 32 x 64 (waves of 16 x 32, more workgroups per CU); 3: 128 x 64 (waves of 64 x 32);
 // 4: 64 x 128 (waves of 32 x 64); 5: as 1 without the XCD order.
+// Where the launch has at most FEW_TILES 64 x 64 tiles (four per compute unit, as many as one holds), 1
+// takes 32 x 32 tiles instead: a workgroup's K loop is a chain of matrix instructions (32 us at K = 192), which
+// four times the workgroups shorten.  Every element sums the same products in the same order, so
+// the results are bitwise those of 64 x 64 (and may follow the number of systems).  One site 1.120 ->
+// 1.057 ms, 32 sites of n = 304 1.183 -> 1.132, 12 systems of n = 2160 18.87 -> 18.48; a limit of one tile per
+// compute unit 18.67, of sixteen 18.66 (200 systems of n = 1424 38.73 -> 39.04).
 void launch_gemm_f64_variant(int variant, const JobDesc* jobs, int njobs, int rows, int cols, int k, int kd,
                              int r_begin, int c_begin, int c_end, double2* work, hipStream_t s) {
-  switch (variant) {
+  const bool few = (int64_t)((rows + 63) / 64) * ((cols + 63) / 64) * njobs <= FEW_TILES;
+  switch (variant == 1 && few ? -1 : variant) {
+    case -1: launch_tiled64<32, 32, 16, 16, true, 16>(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s); break;
     case 1: launch_tiled64<64, 64, 32, 32, true, 8>(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s); break;
     case 2: launch_tiled64<32, 64, 16, 32, true, 8>(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s); break;
     case 3: launch_tiled64<128, 64, 64, 32, true, 8>(jobs, njobs, rows, cols, k, kd, r_begin, c_begin, c_end, work, s); break;
