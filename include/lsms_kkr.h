@@ -265,7 +265,8 @@ int lsms_factors_free(lsms_factors* factors);
  *   A         host [batch] device pointers to row-major n x n complex matrices (read only)
  *   B         host [batch] device pointers to row-major n x nrhs complex right-hand sides (overwritten by X)
  *   nrhs      1 .. 16
- *   precision LSMS_FP64 (or LSMS_SPLIT: FP32 factors, no refinement)
+ *   precision LSMS_FP64 (or LSMS_SPLIT: FP32 factors, no refinement; every update on the FP32 matrix
+ *             cores, also with tiling 19, see LSMS_TUNE_GEMM_F32)
  *   info      device [batch] int32 (out): 0, or k > 0 for an exact zero pivot at column k
  */
 int lsms_batched_lu_solve(lsms_ctx* ctx, int32_t batch, const int32_t* n, void* const* A, void* const* B,
@@ -301,7 +302,7 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * the streaming persistent form, whose next tile's first K chunk is loaded during the current
  * tile's last one, without and with the C tile loaded early; 19: as 2 with each job's tiles
  * numbered in bands of eight tile rows, so one XCD's resident workgroups share few L21 and
- * U12 panels in its L2, and, for wide updates of at least 512 rows, the FP16 matrix cores with every
+ * U12 panels in its L2, and, for wide updates of at least 512 rows in lsms_tau_solve, the FP16 matrix cores with every
  * FP32 operand as a scaled pair of FP16 numbers and FP32 sums; 20: as 13 in bands of eight tile rows); every
  * tiling computes the same update (the FP32 tilings differ in rounding order only; 19's pairs hold
  * the operands to 2^-24 of their value and round its sums less often: its error against FP64 is

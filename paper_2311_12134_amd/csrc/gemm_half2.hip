@@ -16,6 +16,11 @@
 // four, so the sums round less often; the update's error against FP64 is smaller than that of
 // the FP32 matrix-core tilings.
 //
+// Scaling by rows and columns cannot bring every matrix to one size (zero blocks between columns of
+// unlike size suffice), and where it fails small entries are lost beside large ones.  So these
+// kernels run only where an FP64 residual checks the solution (lsms_tau_solve, which falls back to an
+// FP64 LU), not for lsms_batched_lu_solve.
+//
 // Three launches per update and group of jobs: half2_scale_kernel finds s_q, split_half2_kernel writes the pairs of the
 // L21 rows and U12 columns once, in the order the matrix instruction takes its operands, and
 // gemm_half2_kernel multiplies them.  The pairs live in scratch of bounded size, so a wave

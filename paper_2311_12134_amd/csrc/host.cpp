@@ -1600,8 +1600,9 @@ extern "C" int lsms_batched_lu_solve(lsms_ctx* ctx, int32_t batch, const int32_t
     lu_solve_f64(jd, batch, npad_max, (const double2*)abuf, piv, xbuf, 0, 16, 0, tl.group, s);
   } else {
     const Tiling tl = pick_tiling(ctx, prec, npad_max);
-    lu_factor_f32(jd, batch, npad_max, (float2*)abuf, piv, info, s, nullptr, tl, ts,
-                  half2_scratch(ctx, batch, npad_max, tl, s));
+    // never the FP16-pair update (no scratch for it): nothing checks these solutions, and a matrix whose
+    // rows and columns cannot be brought to one size would lose in its pairs what FP32 keeps
+    lu_factor_f32(jd, batch, npad_max, (float2*)abuf, piv, info, s, nullptr, tl, ts, Half2Scratch{});
     lu_solve_f32(jd, batch, npad_max, (const float2*)abuf, piv, xbuf, 0, 16, 0, tl.group, s);
   }
   launch_store_user(jd, batch, npad_max, bptr, nrhs, xbuf, s);
