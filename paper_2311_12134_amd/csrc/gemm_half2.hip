@@ -61,23 +61,31 @@ static inline __host__ __device__ Half2Layout half2_layout(int rows, int cols, i
 
 size_t half2_job_bytes(int rows, int cols, int kd) { return (size_t)half2_layout(rows, cols, kd).bytes; }
 
-// s_q of every K row of U12, one wavefront per row: the exponent of the largest of 64 entries, in
-// four pieces of 16 columns spread over all columns past the group (whatever columns the update is
-// asked for, so that an update in two parts rounds as one does).  An estimate is enough: s_q only
-// has to follow rows that differ by many powers of two.
+// s_q of every K row of U12, one wavefront per row: the exponent of the largest finite entry over all
+// columns past the group (whatever columns the update is asked for, so that an update in two parts
+// rounds as one does).  All of them: a row whose large entries a sample misses would leave the
+// other entries of their columns in FP16's subnormals.  Bound by HBM.
 __global__ __launch_bounds__(256) void half2_scale_kernel(const JobDesc* jobs, int rows, int cols, int k, int kd,
                                                           const float2* work, char* scratch) {
   const JobDesc jd = jobs[blockIdx.y];
   const int c = jd.npad - k - kd, q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (c <= 0 || q >= kd) return;  // c is a multiple of 64
-  const int col = k + kd + (lane >> 4) * ((c - 16) / 3 & ~15) + (lane & 15);
-  const float2 v = work[jd.a_off + (int64_t)(k + q) * jd.npad + col];
-  float a = fmaxf(fabsf(v.x), fabsf(v.y));
+  const float4* row = (const float4*)(work + jd.a_off + (int64_t)(k + q) * jd.npad + k + kd);
+  float a = 0.f;
+  auto take = [&](float x) { a = fmaxf(a, fabsf(x) < INFINITY ? fabsf(x) : 0.f); };
+#pragma unroll 4
+  for (int i = lane; i < c / 2; i += 64) {
+    const float4 v = row[i];
+    take(v.x);
+    take(v.y);
+    take(v.z);
+    take(v.w);
+  }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
   const Half2Layout lay = half2_layout(rows, cols, kd);
   int s = 0;
-  if (a > 0.f && a < INFINITY) (void)frexpf(a, &s);
+  if (a > 0.f) (void)frexpf(a, &s);
   if (lane == 0) ((int*)(scratch + (int64_t)blockIdx.y * lay.bytes + lay.sk))[q] = s;
 }
 

@@ -74,6 +74,16 @@ def pair_update(s, kd, jobs_at_once=None, c_begin=None, c_end=0, lower=False):
     torch.cuda.synchronize()
 
 
+def fp32_update(s, kd, tiling=2):
+    """The same by an FP32 matrix-core tiling."""
+    n = max(s.npad)
+    call = lib()["_ZN4lsms19launch_gemm_f32_anyEiPKNS_7JobDescEiiiiiiiiP%sRKNS_12Half2ScratchEP12ihipStream_t" % _F2]
+    call.restype = None
+    call(tiling, _ptr(s.jobs), len(s.mats), n - kd, n - kd, 0, kd, kd, kd, 0, _ptr(s.work),
+         ctypes.byref(Scratch(None, 0)), _stream())
+    torch.cuda.synchronize()
+
+
 def ldlt(s, tall_rows):
     """The symmetric factorization; panels of at most tall_rows rows by the panel kernel as a whole."""
     size = lib()._ZN4lsms18ldlt_scratch_bytesEi
