@@ -324,7 +324,7 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
         lds_barrier();
         // the pivot row, entry q in lane q
         const T row = sel(lane + jj < W, s_prow[min(lane, W - 1)], T{0, 0});
-        if (bhi == 0u && blo < 0x2000u) {  // perhaps an exact zero (uniform)
+        if (nopiv || (bhi == 0u && blo < 0x2000u)) {  // perhaps an exact zero (uniform; without pivoting the key says nothing)
           const T pv = lane_value(row, 0);
           if (pv.x == 0 && pv.y == 0 && first_zero == 0) first_zero = k + d + 1;
         }
