@@ -19,6 +19,9 @@ __device__ inline void atomic_max_nonneg(double* addr, double v) {
   atomicMax((unsigned long long*)addr, (unsigned long long)__double_as_longlong(v));
 }
 
+// The larger of a norm so far (not NaN) and a modulus; NaN counts as infinite, so that a norm never misses it.
+__device__ inline double norm_max(double m, double v) { return v <= m ? m : v == v ? v : (double)INFINITY; }
+
 __device__ inline double cabs_(double2 v) { return sqrt(v.x * v.x + v.y * v.y); }
 __device__ inline int lch(int L) { return L < 1 ? 0 : L < 4 ? 1 : L < 9 ? 2 : 3; }  // l of channel L
 
@@ -169,7 +172,9 @@ __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(con
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          double m = (double)__builtin_sqrtf((float)(A[s].x * A[s].x + A[s].y * A[s].y));
+          const double m2 = A[s].x * A[s].x + A[s].y * A[s].y;
+          const float f = (float)m2;
+          double m = f < INFINITY ? (double)__builtin_sqrtf(f) : sqrt(m2);  // past FP32's range (members 0.05 bohr apart)
           if (SYM) m *= cabs_(eb[s]);
           rowabs += m;
         }
@@ -207,7 +212,7 @@ __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(con
   if (MNORM) {
     rowabs += __shfl_xor(rowabs, 16);
     rowabs += __shfl_xor(rowabs, 32);
-    if (a < nl) mmax = 1.0 + cabs_(dtab[liz_atom[jd.liz_off + a] * 8 + eoff + lch(lane & 15)]) * rowabs;
+    if (a < nl) mmax = norm_max(1.0, 1.0 + cabs_(dtab[liz_atom[jd.liz_off + a] * 8 + eoff + lch(lane & 15)]) * rowabs);
   }
   // residual entries: lane l, register q -> row 16 a + l / 16 + 4 q, column l % 16
   const int col = lane & 15;
@@ -230,14 +235,14 @@ __global__ __launch_bounds__(256, MNORM && SYM ? 2 : 3) void residual_kernel(con
     double v = cabs_(rv);
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
-    rmax = fmax(rmax, v);
+    rmax = norm_max(rmax, v);
   }
   // ||X||_inf over the workgroup's rows
   double xmax = 0.0;
   if (t < 64) {
     double v = 0.0;
     for (int c = 0; c < 16; ++c) v += cabs_(X[(int64_t)(row0 + t) * NRHS_MAX + c]);
-    xmax = v;
+    xmax = norm_max(0.0, v);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -282,8 +287,8 @@ void launch_residual(const JobDesc* jobs, int njobs, int npad_max, const double2
   }
 }
 
-// Backward error of every pending job; jobs that reach tol are marked done, the others
-// are counted in *pending (one int, cleared by the caller before the launch).  Jobs that
+// Backward error of every pending job; jobs that reach tol are marked done (an infinite norm never
+// is one: 0 or no number as backward error would say nothing), the others are counted in *pending (one int, cleared by the caller before the launch).  Jobs that
 // are flagged already (zero pivot, bad input) are not refined.
 // The condition grows with the system, and whether a solution stops just below tol or a correction
 // (a factor of 1e3 and more) further down is a matter of rounding: at n = 15,440 solutions with
@@ -297,7 +302,8 @@ __global__ void refine_step_kernel(const JobDesc* jobs, int njobs, double* norms
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= njobs || done[j]) return;
   double* nm = norms + j * 8;
-  const double berr = nm[1] / (nm[0] * nm[2] + nm[4]), before = nm[3];
+  const double scale = nm[0] * nm[2] + nm[4], before = nm[3];
+  const double berr = scale < INFINITY ? nm[1] / scale : (double)INFINITY;
   nm[3] = berr;
   const bool again = !last && nm[5] == 0.0 && berr > fmax(tol * GUARD_ROWS / jobs[j].npad, GUARD_BERR) &&
                      berr < 0.1 * before;

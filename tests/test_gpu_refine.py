@@ -77,3 +77,41 @@ def test_residuals_of_small_and_ragged_member_counts(symmetric):
         for a, b in zip(got[:2], ref[:2]):
             assert float((a - b).norm() / b.norm()) <= 1e-11, n
     ctx.close()
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("e_fermi,distance", [(0.65, 3e-2), (0.65, 3e-3), (0.65, 3e-4), (0.65, 1e-6), (0.01, 6.31e-2),
+                                              (0.01, 4e-2), (0.04, 3.16e-2), (0.04, 2e-2)])
+def test_no_solution_is_accepted_on_a_norm_that_is_not_finite(symmetric, e_fermi, distance):
+    """Two of five members so close that moduli of M, or the unpivoted factors, leave FP32's range.  What is
+    returned with info 0 has a backward error that was measured, and holds it against M in 64 bits; the rest is
+    the FP64 LU's."""
+    from oracle import kkr
+    from paper_2311_12134_amd.api import Liz
+    print("[gpu] members %g apart at %g, symmetric %s" % (distance, e_fermi, symmetric), flush=True)
+    pos = np.array([[0, 0, 0], [4, 0, 0], [0, 4, 0], [0, 4, 0], [0, 0, 4]], dtype=np.float64)
+    pos[3] += distance * np.array([0.6, 0.0, 0.8])
+    order = [[i] + [j for j in range(5) if j != i] for i in range(5)]
+    liz = Liz(np.arange(6) * 5, np.concatenate(order).astype(np.int32), np.concatenate([pos[o] - pos[o[0]] for o in order]))
+    ctx = P.Context(0)
+    ctx.set_symmetric(symmetric)
+    atom, dpos = liz.to_device(ctx.device)
+    lo, hi = ([0.1, 0.05, 0.01, 0.001], [0.6, 0.3, 0.06, 0.006]) if e_fermi > 0.5 else (1.3, 1.5)
+    phase = np.random.default_rng(1).uniform(lo, hi, (5, 4))
+    out = ctx.tau_solve(liz, atom, dpos, torch.from_numpy(phase).cuda(), e_fermi, 0.001, precision="split")
+    tau, info, berr = [t.cpu().numpy() for t in out[:2]], out[2].cpu().numpy(), out[3].cpu().numpy()
+    _, _, *kappa = kkr.energies(e_fermi, 0.001)
+    t = kkr.t_matrix(phase, kappa[0])
+    for a in range(5):
+        for e in range(2):
+            assert np.isfinite(tau[e]).all()
+            assert info[a, e] == -1 and berr[a, e] == -1 or info[a, e] == 0 and 0 < berr[a, e] <= 1e-14
+            members = t[e][order[a]]
+            M = kkr.kkr_matrix(liz.pos[5 * a:5 * a + 5], members, kappa[e])
+            X = tau[e][5 * a:5 * a + 5].reshape(80, 16)
+            B = np.zeros((80, 16), dtype=complex)
+            B[:16] = np.diag(kkr.expand_t(members[0]))
+            norm = lambda x: np.abs(x).sum(axis=1).max()
+            # 1e-14, or the FP64 LU's n eps times its growth, and the rounding of M's own entries
+            assert norm(B - M @ X) <= 1e-12 * (norm(M) * norm(X) + norm(B)), (a, e, info[a, e], berr[a, e])
+    ctx.close()
