@@ -18,6 +18,7 @@
 
 #include "../../include/lsms_kkr.h"
 #include "lsms_internal.h"
+#include "scratch.h"
 #include "ylm.h"
 
 using namespace lsms;
@@ -220,20 +221,36 @@ static int tall_scratch(lsms_ctx* ctx, int njobs, int npad_max, TallScratch* ts,
 }
 
 // Scratch of the wide updates of a batch of njobs systems of padded size npad_max on stream s
-// (the pipelined waves' second stream has its own).  Where it cannot be allocated the updates run
-// on the FP32 matrix cores, which need none.
-static Half2Scratch half2_scratch(lsms_ctx* ctx, int njobs, int npad_max, const Tiling& t, hipStream_t s) {
-  Half2Scratch h;
+// (the pipelined waves' second stream has its own): every job's share, or one job's at a time where there
+// is no memory for more, or none, and then the updates run on the FP32 matrix cores.
+static int half2_scratch(lsms_ctx* ctx, int njobs, int npad_max, const Tiling& t, hipStream_t s, Half2Scratch* h) {
+  *h = Half2Scratch{};
   const size_t bytes = t.wide == kDefaultF32Wide ? half2_scratch_bytes(njobs, npad_max, t.group) : 0;
-  if (bytes == 0) return h;
+  if (bytes == 0) return LSMS_OK;
+  const int kd = t.group * NB;
+  const size_t share = half2_job_bytes(npad_max - kd, npad_max - kd, kd);
   DevBuf& b = ctx->half2[ctx->pipe && s == ctx->pipe ? 1 : 0];
-  if (ensure_dev(b, bytes, s) != LSMS_OK) {
-    (void)hipGetLastError();
-    if (b.bytes < half2_job_bytes(npad_max - t.group * NB, npad_max - t.group * NB, t.group * NB)) return h;
+  const int rc = grow_scratch(
+      b, bytes, share, LSMS_E_NOMEM,
+      [](size_t n, void** p) -> int {
+        const hipError_t e = hipMalloc(p, n);
+        if (e == hipErrorOutOfMemory) {
+          (void)hipGetLastError();
+          return LSMS_E_NOMEM;
+        }
+        return e == hipSuccess ? LSMS_OK : fail(LSMS_E_DEVICE, "hipMalloc(%zu) failed: %s", n, hipGetErrorString(e));
+      },
+      [s](void* p) -> int {
+        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(hipFree(p));
+        return LSMS_OK;
+      });
+  if (rc) return rc;
+  if (b.bytes >= share) {
+    h->p = b.p;
+    h->bytes = b.bytes;
   }
-  h.p = b.p;
-  h.bytes = b.bytes;
-  return h;
+  return LSMS_OK;
 }
 
 static int ensure_pinned(lsms_ctx* c, size_t bytes, hipStream_t s) {
@@ -718,7 +735,11 @@ static int factor_and_solve(lsms_ctx* ctx, int precision, const JobDesc* jd, int
   }
   Tiling update = tiling;
   if (sym) update.group = LDLT_GROUP;
-  const Half2Scratch half2 = precision == LSMS_SPLIT ? half2_scratch(ctx, nj, npad_max, update, s) : Half2Scratch{};
+  Half2Scratch half2;
+  if (precision == LSMS_SPLIT) {
+    rc = half2_scratch(ctx, nj, npad_max, update, s, &half2);
+    if (rc) return rc;
+  }
   const SideStream* side = nullptr;
   const bool capture = ctx->graphs && !prof;
   if (!capture) {  // captured graphs keep the single-stream order

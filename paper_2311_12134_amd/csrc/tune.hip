@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "lsms_internal.h"
+#include "scratch.h"
 
 namespace lsms {
 
@@ -101,10 +102,19 @@ int update_autotune(int precision, int kind, int npad, int batch, int group, hip
   const int kd = kind == 1 ? group * NB : (group - 1) * NB;
   const int rows = npad - kd, cols = kind == 1 ? rows : NB, c_end = kind == 1 ? 0 : kd + NB;
   const int nv = f64 ? gemm_f64_variants() : gemm_f32_variants_all();
+  // without memory for any of its scratch, tiling 19 is timed as the FP32 form it then takes
   Half2Scratch half2;
   if (!f64 && kind == 1 && half2_update(rows, kd)) {
-    half2.bytes = half2_scratch_bytes(batch, npad, group);
-    if (hipMalloc(&half2.p, half2.bytes) != hipSuccess) return -1;
+    constexpr int NOMEM = 1;
+    const int rc = grow_scratch(
+        half2, half2_scratch_bytes(batch, npad, group), half2_job_bytes(rows, rows, kd), NOMEM,
+        [](size_t n, void** p) {
+          const hipError_t e = hipMalloc(p, n);
+          if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+          return e == hipSuccess ? 0 : e == hipErrorOutOfMemory ? NOMEM : -1;
+        },
+        [](void*) { return 0; });
+    if (rc) return -1;
   }
   *best = -1;
   for (int v = 0; v < nv; ++v) {
