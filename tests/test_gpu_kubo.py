@@ -89,3 +89,18 @@ def test_no_members_give_zero():
     ptr = np.array([0, ptr[1], ptr[1], ptr[3]], dtype=np.int64)
     got = _run(ptr, atom, species, J, tau, True)
     assert (got[1] == 0).all() and (got[0] != 0).all()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_no_members_give_zero_whatever_the_currents(value):
+    """A skipped atom's species may have no finite currents: it contributes nothing all the same."""
+    ptr, atom, species, J, tau = _inputs(3, 4, 1, 8)
+    ptr = np.array([0, ptr[1], ptr[1], ptr[3]], dtype=np.int64)
+    J = np.concatenate([J, np.full_like(J, value)])
+    atom[atom == 1] = 0
+    for tensor in (False, True):
+        want = _run(ptr, atom, species, J, tau, tensor)
+        species[1] = 1
+        got = _run(ptr, atom, species, J, tau, tensor)
+        species[1] = 0
+        assert (got[1] == 0).all() and np.array_equal(got, want) and np.isfinite(got).all()
