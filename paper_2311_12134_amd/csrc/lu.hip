@@ -101,10 +101,14 @@ __device__ inline double2 pivot_inverse(double2 a, float2) {
   return make_double2(a.x * rn, -a.y * rn);
 }
 __device__ inline double2 pivot_inverse(double2 a, double2) {
-  const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(a.x), fabs(a.y)));
+  const double m = fmax(fabs(a.x), fabs(a.y));
+  const int e = -__builtin_amdgcn_frexp_exp(m);
   const double x = __builtin_amdgcn_ldexp(a.x, e), y = __builtin_amdgcn_ldexp(a.y, e);
   const double rn = recip(__builtin_fma(x, x, y * y));
-  return make_double2(__builtin_amdgcn_ldexp(x * rn, e), __builtin_amdgcn_ldexp(-y * rn, e));
+  // one infinite component: 0, as a division gives (the Newton steps would make it NaN)
+  const double z = 0.0 * fmin(fabs(a.x), fabs(a.y));
+  const bool inf = m == INFINITY;
+  return make_double2(inf ? z : __builtin_amdgcn_ldexp(x * rn, e), inf ? -z : __builtin_amdgcn_ldexp(-y * rn, e));
 }
 
 // a - b c for the leaf's rank-1 updates: each component as two fused multiply-adds (two

@@ -67,6 +67,27 @@ def test_zero_pivot_is_reported_at_its_column(ctx, precision):
     assert list(info) == [c + 1 for c in cols]
 
 
+@pytest.mark.parametrize("chunk", [2048, 64])  # with 64, panels of more than 128 rows by tournament
+def test_infinite_pivots_in_fp64(ctx, chunk):
+    """An infinite entry on the diagonal takes its unknown out of the system: that one is 0 and the others are those of
+    the system without it (backward error of the LU, n eps, times a condition below 20)."""
+    rng = np.random.default_rng(7)
+    ctx.set_tslu_chunk(chunk)
+    try:
+        for n in (8, 70, 300, 700):
+            for where in ([0], [5], [n - 1], [0, 3, n // 2]):
+                print("[gpu] infinite pivots", chunk, n, where, flush=True)
+                m = 0.5 * (rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))) / np.sqrt(2 * n) + np.eye(n)
+                keep = np.setdiff1d(np.arange(n), where)
+                ref = np.linalg.solve(m[np.ix_(keep, keep)], np.ones((len(keep), 1)))
+                m[where, where] = np.inf
+                (x,), info = _solve(ctx, [m], [np.ones((n, 1), dtype=np.complex128)], "fp64")
+                assert info[0] == 0 and (x[where] == 0).all()
+                assert np.abs(x[keep] - ref).max() <= 20 * n * 2.0 ** -53 * np.abs(ref).max()
+    finally:
+        ctx.set_tslu_chunk(2048)
+
+
 def test_few_tall_systems_look_ahead_bitwise(ctx):
     """One LIZ of 259 members (n = 4160, tournament panels), where the next group's first panel runs on a stream of
     its own, against graph replay, which keeps one stream."""
