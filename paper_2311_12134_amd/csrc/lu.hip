@@ -89,26 +89,31 @@ __device__ inline double2 lane_value(double2 x, int l) {
 
 // Inverse of a pivot in FP64, conj(a) / |a|^2.  Values stored in FP32 have squared magnitudes well
 // inside the FP64 range; FP64 values are first scaled by a power of two that brings the larger
-// component to [1/2, 1).  1 / |a|^2 by two Newton steps on the hardware's reciprocal (24 bits or
-// more, so the second step ends at FP64's own rounding), a third of the chain of a division.
-__device__ inline double recip(double n) {
-  double r = __builtin_amdgcn_rcp(n);
-  r = __builtin_fma(__builtin_fma(-n, r, 1.0), r, r);
-  return __builtin_fma(__builtin_fma(-n, r, 1.0), r, r);
-}
+// component to [1/2, 1).  1 / |a|^2 by Newton steps on the hardware's reciprocal (24 bits or more), a
+// third of the chain of a division: two of them for values stored in FP32, which end at FP64's own
+// rounding.
+__device__ inline double recip_step(double n, double r) { return __builtin_fma(__builtin_fma(-n, r, 1.0), r, r); }
 __device__ inline double2 pivot_inverse(double2 a, float2) {
-  const double rn = recip(__builtin_fma(a.x, a.x, a.y * a.y));
+  const double n = __builtin_fma(a.x, a.x, a.y * a.y);
+  const double rn = recip_step(n, recip_step(n, __builtin_amdgcn_rcp(n)));
   return make_double2(a.x * rn, -a.y * rn);
 }
+// FP64 values: one step on 1 / |a|^2, then one on the complex inverse, z (2 - a z), so that the inverse of a real or an
+// imaginary pivot is the rounded quotient: rows that are exact multiples of the pivot row then cancel
+// exactly where they do with a division, and a singular matrix of such rows is reported as one.
 __device__ inline double2 pivot_inverse(double2 a, double2) {
   const double m = fmax(fabs(a.x), fabs(a.y));
   const int e = -__builtin_amdgcn_frexp_exp(m);
   const double x = __builtin_amdgcn_ldexp(a.x, e), y = __builtin_amdgcn_ldexp(a.y, e);
-  const double rn = recip(__builtin_fma(x, x, y * y));
+  const double n = __builtin_fma(x, x, y * y);
+  const double rn = recip_step(n, __builtin_amdgcn_rcp(n));
+  const double u = x * rn, v = -y * rn;
+  const double er = __builtin_fma(y, v, __builtin_fma(-x, u, 1.0)), ei = __builtin_fma(-x, v, -y * u);
+  const double zr = __builtin_fma(u, er, __builtin_fma(-v, ei, u)), zi = __builtin_fma(u, ei, __builtin_fma(v, er, v));
   // one infinite component: 0, as a division gives (the Newton steps would make it NaN)
   const double z = 0.0 * fmin(fabs(a.x), fabs(a.y));
   const bool inf = m == INFINITY;
-  return make_double2(inf ? z : __builtin_amdgcn_ldexp(x * rn, e), inf ? -z : __builtin_amdgcn_ldexp(-y * rn, e));
+  return make_double2(inf ? z : __builtin_amdgcn_ldexp(zr, e), inf ? -z : __builtin_amdgcn_ldexp(zi, e));
 }
 
 // a - b c for the leaf's rank-1 updates: each component as two fused multiply-adds (two

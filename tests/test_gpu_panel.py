@@ -67,6 +67,16 @@ def test_zero_pivot_is_reported_at_its_column(ctx, precision):
     assert list(info) == [c + 1 for c in cols]
 
 
+def test_multiples_of_the_pivot_row_cancel_as_with_a_division(ctx):
+    """Constant real and imaginary 2 x 2 matrices in FP64: the second pivot is v - (v (1 / v)) v with a correctly
+    rounded 1 / v, an exact zero for most v."""
+    values = [v * f for v in range(1, 300) for f in (1, 1j, -1, 0.1)]
+    _, info = _solve(ctx, [np.full((2, 2), v, dtype=np.complex128) for v in values],
+                     [np.ones((2, 1), dtype=np.complex128)] * len(values), "fp64")
+    size = np.abs(np.array(values))
+    assert np.array_equal(info, np.where(size * (1.0 / size) == 1.0, 2, 0))
+
+
 @pytest.mark.parametrize("chunk", [2048, 64])  # with 64, panels of more than 128 rows by tournament
 def test_infinite_pivots_in_fp64(ctx, chunk):
     """An infinite entry on the diagonal takes its unknown out of the system: that one is 0 and the others are those of
