@@ -304,7 +304,7 @@ __global__ void refine_step_kernel(const JobDesc* jobs, int njobs, double* norms
   double* nm = norms + j * 8;
   const double scale = nm[0] * nm[2] + nm[4], before = nm[3];
   const double berr = scale < INFINITY ? nm[1] / scale : (double)INFINITY;
-  nm[3] = berr;
+  nm[3] = job_info[j] != 0 && !(berr < INFINITY) ? 0.0 : berr;  // flagged systems report 0, not infinity
   const bool again = !last && nm[5] == 0.0 && berr > fmax(tol * GUARD_ROWS / jobs[j].npad, GUARD_BERR) &&
                      berr < 0.1 * before;
   if ((berr <= tol && !again) || job_info[j] != 0) {

@@ -115,3 +115,22 @@ def test_no_solution_is_accepted_on_a_norm_that_is_not_finite(symmetric, e_fermi
             # 1e-14, or the FP64 LU's n eps times its growth, and the rounding of M's own entries
             assert norm(B - M @ X) <= 1e-12 * (norm(M) * norm(X) + norm(B)), (a, e, info[a, e], berr[a, e])
     ctx.close()
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_systems_with_bad_inputs_report_no_backward_error(symmetric):
+    """Systems flagged for a NaN or an infinite phase shift report 0, the others what was measured."""
+    grid = np.array([(i, j, k) for i in range(3) for j in range(3) for k in range(2)], dtype=np.float64) * 6.0
+    ctx = P.Context(0)
+    ctx.set_symmetric(symmetric)
+    liz = P.build_liz(grid, None, 6.1)
+    atom, dpos = liz.to_device(ctx.device)
+    phase = np.random.default_rng(3).uniform(-0.5, 0.5, (len(grid), 4))
+    phase[0, 1], phase[9, 3] = np.nan, np.inf
+    touched = np.array([np.isin([0, 9], liz.atom[b:e]).any() for b, e in zip(liz.ptr[:-1], liz.ptr[1:])])
+    out = ctx.tau_solve(liz, atom, dpos, torch.from_numpy(phase).cuda(), 0.6, 0.01, precision="split")
+    info, berr = out[2].cpu().numpy(), out[3].cpu().numpy()
+    assert touched.any() and not touched.all()
+    assert (info[touched] == -2).all() and (berr[touched] == 0).all()
+    assert (info[~touched] == 0).all() and (0 < berr[~touched]).all() and (berr[~touched] <= 1e-14).all()
+    ctx.close()
