@@ -199,9 +199,8 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
   constexpr int SEG = IB * (int)sizeof(T) < 128 ? IB : 128 / (int)sizeof(T);  // columns moved per staged access
   constexpr int CPR = SEG * (int)sizeof(T) / 16, RPI = 64 / CPR;  // 16-byte chunks per row, rows per access
   constexpr int PER = 16 / (int)sizeof(T);                        // elements per chunk
-  constexpr bool ONE = IB == NB;                                  // the whole panel is one leaf
   constexpr int BB = IB >= 32 ? 8 : 4;                            // columns per block of the leaf
-  static_assert(IB / BB <= 4 && BB % 2 == 0, "the blocks below; buffers alternate across blocks");
+  static_assert(IB < NB && IB / BB <= 4 && BB % 2 == 0, "the blocks below; buffers alternate across blocks");
   // the leaf's register that holds column j once it is factored
   auto reg_of = [](int j) { return IB - (j / BB + 1) * BB + j % BB; };
 
@@ -209,9 +208,9 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
   __shared__ T s_inv[NW];
   __shared__ __align__(16) T s_prow[IB];
   __shared__ int s_pivall[NB];
-  __shared__ T s_L11[ONE ? 1 : IB][IB + 1];
-  __shared__ T s_U[ONE ? 1 : IB][ONE ? 1 : NB - IB];
-  __shared__ unsigned short s_org[ONE ? 1 : S * PT];  // original row at each position, over all leaves
+  __shared__ T s_L11[IB][IB + 1];
+  __shared__ T s_U[IB][NB - IB];
+  __shared__ unsigned short s_org[S * PT];  // original row at each position, over all leaves
   __shared__ int s_lpos[2 * IB], s_lorg[2 * IB], s_lcnt;
   __shared__ int s_row[PT];
   // The next leaf stays on chip for 16-wide FP32 leaves of three or four row slots (the other
@@ -226,9 +225,7 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
   T v[S][IB];
   int pos[S];
   int first_zero = 0;
-  if constexpr (!ONE) {
-    for (int i = t; i < S * PT; i += PT) s_org[i] = (unsigned short)i;
-  }
+  for (int i = t; i < S * PT; i += PT) s_org[i] = (unsigned short)i;
 
   const int ch = lane % CPR, rsub = lane / CPR;
   for (int c = 0; c < NB / IB; ++c) {
@@ -380,7 +377,7 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
         s_lpos[i] = pos[s];
         s_lorg[i] = home;
       }
-      if (!ONE && pos[s] >= cl && pos[s] < cl + IB) {
+      if (pos[s] >= cl && pos[s] < cl + IB) {
 #pragma unroll
         for (int q = 0; q < IB; ++q) s_L11[pos[s] - cl][q] = v[s][reg_of(q)];
       }
@@ -415,8 +412,8 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
       ldx = here();
       const int ncols = left + NB - IB;
       unsigned short org = 0;
-      if (!ONE && t < cnt) org = s_org[s_lorg[t]];
-      for (int c0 = 0; c0 < ncols || c0 == 0; c0 += 64) {
+      if (t < cnt) org = s_org[s_lorg[t]];
+      for (int c0 = 0; c0 < ncols; c0 += 64) {
         const int cc = c0 + lane, cr = cc - left;
         const int colx = cc < left ? k - left + cc : k + (cr < cl ? cr : cr + IB);
         T held[HELD];
@@ -434,7 +431,7 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
           if (i < cnt && cc < ncols) *at(s_lpos[i], colx, ldx) = held[u];
         }
       }
-      if (!ONE && t < cnt) s_org[s_lpos[t]] = org;
+      if (t < cnt) s_org[s_lpos[t]] = org;
     }
     __syncthreads();
     if (w > 0) {
@@ -591,10 +588,9 @@ __global__ __launch_bounds__(PT, 2) void panel_kernel(const JobDesc* jobs, int k
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    // with one leaf the row in slot s ended at pos[s]; with several, position t + s PT holds s_org[]
-    const int at = ONE ? pos[s] : t + s * PT;
-    if (at < 0 || at >= nrows) continue;
-    const int org = ONE ? t + s * PT : s_org[t + s * PT];
+    const int at = t + s * PT;
+    if (at >= nrows) continue;
+    const int org = s_org[at];
     int i = at;
     if (at >= NB) {
       if (at == org) continue;
