@@ -702,15 +702,17 @@ void launch_fallback_status(int nf, const JobDesc* fjobs, const int32_t* finfo, 
 // and right-hand sides are read from device memory at replay, after the caller's stream has
 // written them.
 // The look-ahead stream: where asked for, and for split-mode waves of few tall systems, whose tournament
-// panels leave most compute units idle (at most one workgroup each in their first round).  Results are bitwise
-// the same.  n = 15,440: 2 systems 208 -> 197 ms, 8 467 -> 450, 20 961 -> 950, with two thirds of the compute units
-// busy and more no gain; FP64 none (511 -> 514 ms); systems without tournament panels lose
-// as often as they gain (n = 2160: 2 systems 9.6 -> 9.9 ms, 12 11.3 -> 11.0, 96 27.6 -> 28.2).
+// panels leave compute units idle: up to two thirds of them busy in the first round of the first panel (one
+// workgroup per chunk).  Results are bitwise the same.  ms a solve on one stream and with the look-ahead, by
+// systems (and chunks, of 256 compute units): n = 15,440: 2 (22) 194 -> 185, 8 (88) 444 -> 436, 16 (176) 766 -> 764, 20 (220)
+// 922 -> 926, 22 (242) 1002 -> 1013; n = 4528: 20 (60) 61.6 -> 58.9, 40 (120) 91.3 -> 89.9, 56 (168) 115.4 -> 115.0,
+// 72 (216) 137.7 -> 139.4, 82 (246) 152.7 -> 155.0.  FP64 gains nothing (511 -> 514 ms); systems without
+// tournament panels lose as often as they gain (n = 2160: 2 systems 9.6 -> 9.9 ms, 12 11.3 -> 11.0, 96 27.6 -> 28.2).
 static int side_stream(lsms_ctx* ctx, int precision, int njobs, int npad_max, const TallScratch& ts, bool timed,
                        const SideStream** out) {
   *out = nullptr;
   const bool few_tall = precision == LSMS_SPLIT && ts.base && !timed &&
-                        (int64_t)njobs * ((npad_max + ts.chunk - 1) / ts.chunk) <= ctx->cu_count;
+                        3 * (int64_t)njobs * ((npad_max + ts.chunk - 1) / ts.chunk) <= 2 * (int64_t)ctx->cu_count;
   if (!ctx->lookahead && !few_tall) return LSMS_OK;
   if (!ctx->side.panel_done) {
     if (!ctx->side.stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->side.stream, hipStreamNonBlocking));
