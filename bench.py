@@ -10,11 +10,12 @@ Inputs are synthetic and seeded (no dataset); they live in HBM before the timed 
 
 Prints one JSON line.  `roofline` is the wide trailing update's achieved algorithmic
 TFLOP/s (8 m c K complex flops per job and launch, over its HIP-event launch time on its own
-stream) against the peak of the matrix cores its tiling runs on: 157.3 TFLOP/s for FP32 MFMA,
-2516.6 / 3 for the default, which takes an FP32 product as three FP16 ones; with the HBM
-traffic recorded for that kernel source and launch shape (path_frac_of_peak sets the whole
-path against the FP32 MFMA peak); `cpu_baseline` is the oracle's rate on a bounded sample of
-the same workload on the host cores.
+stream) against the peak of the matrix cores it runs on: 157.3 TFLOP/s for FP32 MFMA, 2516.6 / 3
+where the default tiling takes an FP32 product as three FP16 ones (updates of at least 512 rows),
+and the rate of both in turn where a step has both; with the HBM traffic recorded for that
+kernel source and launch shape.  path_frac_of_peak (FP64 only: the split path runs on FP16, FP32 and
+FP64 matrix cores) sets the whole path against the FP64 MFMA peak; `cpu_baseline` is the oracle's
+rate on a bounded sample of the same workload on the host cores.
 """
 
 import argparse
@@ -47,8 +48,25 @@ def gemm_source(precision, tiling):
     return os.path.join(CSRC, name)
 
 
-def update_peak(precision, tiling):
-    return PEAK_FP64_MFMA if precision != "split" else PEAK_HALF2 if tiling == 19 else PEAK_FP32_MFMA
+def pair_share(tiling, sizes, group):
+    """Share of the wide updates' algorithmic flops that the default tiling does from FP16 pairs: those of at least
+    512 (padded) rows.  sizes: n of every system (a wave's systems are nearly alike)."""
+    pairs = total = 0.0
+    for n, count in zip(*np.unique(np.asarray(sizes, dtype=np.int64), return_counts=True)):
+        npad, kd = (int(n) + 63) // 64 * 64, 64 * group
+        for begin in range(kd, npad, kd):
+            f = 8.0 * max(int(n) - begin, 0) ** 2 * kd * int(count)
+            total += f
+            pairs += f if tiling == 19 and npad - begin >= 512 else 0.0
+    return pairs / total if total else 0.0
+
+
+def update_peak(precision, tiling, sizes, group):
+    """The rate of the wide updates with each at the peak of its matrix cores."""
+    if precision != "split":
+        return PEAK_FP64_MFMA
+    share = pair_share(tiling, sizes, group)
+    return 1.0 / (share / PEAK_HALF2 + (1.0 - share) / PEAK_FP32_MFMA)
 
 
 # HBM bytes per launch of the trailing-update kernel on this workload, from two rocprofv3
@@ -210,17 +228,17 @@ def paper_scale_leg(P, torch, ctx, n_sample, precision, tiling, ldlt=False):
     ctx.set_profiling(False)
     n = 16 * int(np.diff(liz.ptr).max())
     alg = n_sample * 2.0 * ((8.0 / 3.0) * n**3 + 128.0 * n**2)
-    peak = PEAK_FP32_MFMA if precision == "split" else PEAK_FP64_MFMA
+    group = ctx.knob("group_f32" if precision == "split" else "group_f64")
     res = {"workload": "bcc16000: random bcc A0.5B0.5, 16000 atoms, LIZ 965 sites (n = %d), %d seeded centres, "
                        "both energies, eta %g Ry" % (n, n_sample, eta),
            "value": n_sample / el, "unit": "atoms/s", "ms_per_step": 1e3 * el, "precision": precision,
-           "path_tflops_alg": alg / el / 1e12, "path_frac_of_peak": alg / el / peak,
+           "path_tflops_alg": alg / el / 1e12,
            "info_nonzero": int((info.cpu().numpy()[centres] != 0).sum()),
            "berr_max": float(berr.cpu().numpy()[centres].max())}
     if gl:
         res["trailing_update"] = {"launches": gl, "avg_launch_ms": gms / gl,
                                   "achieved_tflops": gf / (gms / 1e3) / 1e12,
-                                  "frac": gf / (gms / 1e3) / update_peak(precision, tiling)}
+                                  "frac": gf / (gms / 1e3) / update_peak(precision, tiling, [n], group)}
     log("paper-scale leg: %d atoms of bcc16000 (n = %d) in %.2f s: %.2f atoms/s" % (n_sample, n, el, n_sample / el))
     if ldlt and precision == "split":
         # the same sample through the symmetric form and L D L^T (reported apart from the LU)
@@ -282,16 +300,22 @@ def tune_all(ctx, npads, batch=256):
                                  "ms_small_large_per_height": [round(m, 3) for m in ms]}}
 
 
-def gemm_roofline(ctx, precision, workload, tiling, timed_in):
+def gemm_roofline(ctx, precision, workload, tiling, sizes, timed_in):
     """The wide trailing update's roofline entry from the launches recorded while profiling."""
     gemm_ms, launches, flops, alg_bytes = ctx.kernel_stats(kind=1)
     if not launches:
         return None
     avg_s = gemm_ms / launches / 1e3
     achieved = flops / launches / avg_s
-    peak = update_peak(precision, tiling)
+    group = ctx.knob("group_f32" if precision == "split" else "group_f64")
+    peak = update_peak(precision, tiling, sizes, group)
+    share = pair_share(tiling, sizes, group) if precision == "split" else 0.0
     kname = (F32_TILINGS if precision == "split" else F64_TILINGS).get(tiling, "tiling %d" % tiling)
-    with open(gemm_source(precision, tiling), "rb") as f:
+    if precision == "split" and tiling == 19:
+        # below 512 rows the same tiling runs on the FP32 matrix cores
+        fp32 = "gemm_f32_3m_tiled<64,64,32,32,xcd,bands of 8>"
+        kname = fp32 if share == 0.0 else kname if share == 1.0 else "%s (%.3f of the flops), %s" % (kname, share, fp32)
+    with open(gemm_source(precision, tiling if share > 0.0 or tiling != 19 else 2), "rb") as f:
         digest = hashlib.sha256(f.read()).hexdigest()
     rec = TRAFFIC.get((precision, workload, tiling))
     same_shape = rec is not None and abs(alg_bytes / launches / rec["alg_bytes_per_launch"] - 1) < 1e-3
@@ -299,7 +323,7 @@ def gemm_roofline(ctx, precision, workload, tiling, timed_in):
     return {"kernel": kname, "bound": "mfma", "achieved": achieved / 1e12, "peak": peak / 1e12,
             "timed_in": timed_in, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
             "launches": launches, "avg_launch_ms": 1e3 * avg_s, "alg_flops_per_launch": flops / launches,
-            "alg_bytes_per_launch": alg_bytes / launches}
+            "alg_bytes_per_launch": alg_bytes / launches, "fp16_pair_flops_share": share}
 
 
 def main():
@@ -464,7 +488,8 @@ def main():
                  "what": "the same steps with every launch issued eagerly (trailing-update launches timed)"}
         log("eager region: %.1f ms/step" % (1e3 * el_e / args.steps))
     tiling = tiling_in_effect(args.precision)
-    roof = gemm_roofline(ctx, args.precision, args.workload, tiling,
+    sizes = 16 * np.diff(liz.ptr)
+    roof = gemm_roofline(ctx, args.precision, args.workload, tiling, sizes,
                          "the eager timed region" if args.graphs else "the timed region")
     narrow_ms, narrow_launches, narrow_flops, _ = ctx.kernel_stats(kind=0)
     ctx.set_profiling(False)
@@ -476,12 +501,12 @@ def main():
 
     n_true = 16 * np.diff(liz.ptr).astype(np.float64)
     alg_flops_step = float(np.sum(2.0 * ((8.0 / 3.0) * n_true**3 + 128.0 * n_true**2)))
-    peak = PEAK_FP32_MFMA if args.precision == "split" else PEAK_FP64_MFMA
     timed_etas = sorted({etas[i % len(etas)] for i in range(max(args.steps, 1))}, reverse=True)
     out = {"metric": METRIC, "value": value, "unit": "atoms/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
            "vs_baseline": None,
-           "dtype": "fp32 LU updates and refinement solves + fp64 pivot keys/residuals/solution" if args.precision == "split" else "f64",
+           "dtype": ("fp32 LU (wide updates from fp16 pairs, fp32 sums) and refinement solves + fp64 pivot "
+                     "keys/residuals/solution") if args.precision == "split" else "f64",
            "data": "synthetic (seeded structure, phase shifts and current matrices)",
            "config": {"workload": "%s: %s, %d atoms, LIZ %d-%d atoms, lmax 3, eF %.2f Ry, eta cycling %s Ry"
                       % (w["name"], w["lattice"], n_atoms, int(n_true.min() / 16), int(n_true.max() / 16),
@@ -490,10 +515,10 @@ def main():
                       "panels_per_group": ctx.knob("group_f32" if args.precision == "split" else "group_f64"),
                       "pipeline": args.pipeline, "workspace_frac": args.workspace_frac or 0.6,
                       "parallelism": "single GPU, all atoms batched"},
-           "path_tflops_alg": alg_flops_step * args.steps / elapsed / 1e12,
-           "path_frac_of_peak": alg_flops_step * args.steps / elapsed / peak}
+           "path_tflops_alg": alg_flops_step * args.steps / elapsed / 1e12}
+    if args.precision != "split":
+        out["path_frac_of_peak"] = alg_flops_step * args.steps / elapsed / PEAK_FP64_MFMA
     if eager is not None:
-        eager["path_frac_of_peak"] = alg_flops_step * args.steps / (1e-3 * eager["ms_per_step"] * args.steps) / peak
         out["eager"] = eager
     if tune is not None:
         out["autotune"] = tune
@@ -515,7 +540,7 @@ def main():
         step(0, "fp64", fp64_out)
         torch.cuda.synchronize()
         t64 = timed("fp64", fp64_out, len(etas), False, True)
-        roof64 = gemm_roofline(ctx, "fp64", args.workload, tiling_in_effect("fp64"), "the FP64 steps")
+        roof64 = gemm_roofline(ctx, "fp64", args.workload, tiling_in_effect("fp64"), sizes, "the FP64 steps")
         ctx.set_profiling(False)
         fp64_ms = 1e3 * t64 / len(etas)
         out["fp64_ms_per_step"] = fp64_ms

@@ -61,7 +61,8 @@ typedef enum {
 
 typedef enum {
   LSMS_FP64 = 0,  /* whole factorization and solve in FP64 */
-  LSMS_SPLIT = 1  /* FP32 LU updates, FP64 pivot selection, residuals, refinement */
+  LSMS_SPLIT = 1  /* FP32 LU (wide updates from pairs of FP16 numbers, FP32 sums), FP64 pivot
+                     selection, residuals, refinement */
 } lsms_precision;
 
 /* Per-job status codes written to info[] by lsms_tau_solve. */
@@ -159,6 +160,8 @@ int lsms_build_liz_subset(lsms_ctx* ctx, int32_t n_atoms, const double* pos, con
  * tournament panels and, in split mode, at most 1 GiB per stream (or one system's share, 4100
  * npad bytes, if that is more) for the operand pairs of the wide updates; without memory for those
  * the updates run on the FP32 matrix cores.
+ * In split mode the rounding of a system's factors may depend on the largest system of its wave;
+ * the tolerance it is refined to does not.
  * An atom whose LIZ is empty (liz_ptr[a + 1] == liz_ptr[a]) is skipped: no system is
  * solved for it and its info and berr are 0 (not allowed with keep).  This lets a
  * caller solve a subset of a structure's atoms with the structure's phase array.
@@ -284,7 +287,9 @@ int lsms_batched_lu_solve(lsms_ctx* ctx, int32_t batch, const int32_t* n, void* 
  * LSMS_TUNE_GROUP_F32 / _F64), kind 0 the narrow updates of a panel's columns within its
  * group (K = 64, 128, .. 64 (G - 1)), -1 both.  A launch updates,
  * in every system, the unpadded block of m rows and c columns: 8 m c K flops (the
- * standard complex count; the split mode executes 3/4 of it on the matrix cores) and
+ * standard complex count; of a complex product the matrix cores execute four real FP64 products in FP64 mode,
+ * three FP32 ones in split mode, or twelve FP16 ones where its wide updates take pairs, see
+ * LSMS_TUNE_GEMM_F32) and
  * es (m K + K c + 2 m c) bytes, es = 8 (split) or 16 (FP64).  All outputs are host
  * scalars; the call returns LSMS_E_ARG for a NULL pointer or an unknown kind.
  */
@@ -305,8 +310,10 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * U12 panels in its L2, and, for wide updates of at least 512 rows in lsms_tau_solve, the FP16 matrix cores with every
  * FP32 operand as a scaled pair of FP16 numbers and FP32 sums; 20: as 13 in bands of eight tile rows); every
  * tiling computes the same update (the FP32 tilings differ in rounding order only; 19's pairs hold
- * the operands to 2^-24 of their value and round its sums less often: its error against FP64 is
- * the smaller one).  Host-side setting of the context, no device work; returns
+ * the operands to 2^-23 of their value and a product to 2^-21, entries more than 2^16 times smaller than
+ * the largest of their row or column less well, and round the sums less often: on random
+ * entries its error against FP64 measured 0.6 of the FP32 tilings', on the least favourable ones twice
+ * as much).  Host-side setting of the context, no device work; returns
  * LSMS_E_ARG for an unknown knob or value.  lsms_get_tuning reports the tiling in effect.
  */
 #define LSMS_TUNE_GEMM_F32 0

@@ -173,7 +173,7 @@ static void launch_tiled64(const JobDesc* jobs, int njobs, int rows, int cols, i
 
 int gemm_f64_variants() { return 6; }
 
-constexpr int64_t FEW_TILES = 4 * 256;
+constexpr int64_t FEW_TILES = 4 * 256;  // an MI355X's 256 compute units; on fewer (a partition) only the time would change
 
 // 0: the single-buffered 64 x 64 kernel (gemm.hip); 1: 64 x 64, two LDS stages of K = 8, XCD
 // order; 2: 32 x 64 (waves of 16 x 32, more workgroups per CU); 3: 128 x 64 (waves of 64 x 32);

@@ -34,3 +34,17 @@ def test_traffic_records_belong_to_the_current_trailing_update_sources():
     # tiles in bands of eight rows) must stay close to the algorithmic bytes
     rec = bench.TRAFFIC[("split", "fcc4000", 19)]
     assert rec["bytes_per_launch"] / rec["alg_bytes_per_launch"] < 1.3
+
+
+def test_update_peak_follows_the_matrix_cores_that_run():
+    """The default split tiling takes FP16 pairs from 512 rows on: none at n = 304, all but the last updates at
+    n = 2160 (1904 rows down to 640; 384 and 128 rows on the FP32 cores); other tilings never."""
+    import bench
+    fp32, half = bench.PEAK_FP32_MFMA, bench.PEAK_HALF2
+    assert bench.pair_share(19, [304] * 3, 4) == 0.0 and abs(bench.update_peak("split", 19, [304], 4) / fp32 - 1) < 1e-12
+    assert bench.pair_share(2, [2160], 4) == 0.0 and bench.update_peak("fp64", 1, [2160], 4) == bench.PEAK_FP64_MFMA
+    rows = [2160 - 256 * g for g in range(1, 9)]
+    share = sum(m * m for m in rows[:6]) / sum(m * m for m in rows)
+    assert abs(bench.pair_share(19, [2160] * 5, 4) - share) < 1e-12 and 0.97 < share < 1.0
+    peak = bench.update_peak("split", 19, [2160], 4)
+    assert fp32 < peak < half and abs(1 / peak - (share / half + (1 - share) / fp32)) < 1e-20

@@ -165,6 +165,7 @@ def test_unrefined_solutions(radius):
     pairs no less exact than with an FP32 tiling, up to the scatter between two roundings (a factor of 1.5), in
     systems of up to 832, 1088 and 1472 rows, and a system in a wave of unlike ones as exact as by itself."""
     import paper_2311_12134_amd as P
+    from paper_2311_12134_amd.api import Liz
     liz, phase = _cluster(radius)
     ctx = P.Context(0)
     atom, dpos = liz.to_device(ctx.device)
@@ -182,6 +183,14 @@ def test_unrefined_solutions(radius):
     pair, fp32 = errors(19), errors(2)
     assert (pair != fp32).any()
     assert (pair <= 1.5 * fp32.max()).all(), (pair, fp32)
+    ctx.set_gemm_tiling(19)
+    for c in np.flatnonzero(np.diff(liz.ptr)):  # by itself, where a small system keeps to the FP32 tiling
+        part, b = slice(liz.ptr[c], liz.ptr[c + 1]), np.zeros(len(liz.ptr), np.int64)
+        b[c + 1:] = liz.ptr[c + 1] - liz.ptr[c]
+        one = Liz(b, liz.atom[part], liz.pos[part])
+        a1, p1 = one.to_device(ctx.device)
+        tp = ctx.tau_solve(one, a1, p1, phase, 0.65, 0.01, precision="split", refine_tol=1.0, max_refine=0)[0]
+        assert np.linalg.norm(tp.cpu().numpy() - want[part]) <= 1.5 * fp32.max() * np.linalg.norm(want[part])
     ctx.close()
 
 
