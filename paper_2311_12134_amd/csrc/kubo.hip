@@ -54,11 +54,6 @@ __global__ __launch_bounds__(256) void kubo_trace_kernel(int n_atoms, const int6
       for (int mu = 0; mu < (TENSOR ? 3 : 1); ++mu) out[3 * mu] = make_double2(NAN, NAN);
     return;
   }
-  if (nl == 0) {  // nothing to sum (the trace of J0 with no Z would still carry an infinity or NaN of J0)
-    if (lane == 0)
-      for (int mu = 0; mu < (TENSOR ? 3 : 1); ++mu) out[3 * mu] = make_double2(0.0, 0.0);
-    return;
-  }
   const int ii = lane & 15, kq = lane >> 4;
   const double2* T1 = (z1 ? tau_minus : tau_plus) + off * NL * NL + lane;
   const double2* T2 = (z2 ? tau_minus : tau_plus) + off * NL * NL + lane;
@@ -82,9 +77,12 @@ __global__ __launch_bounds__(256) void kubo_trace_kernel(int n_atoms, const int6
     for (int s = 0; s < S; ++s) u[s] = Jc[(int64_t)sa * 12 * NL * NL + 4 * s];
   };
   d4 sr = {0, 0, 0, 0}, si = {0, 0, 0, 0};  // Z
-  int cur = member_species(0);
-  load_j(cur, ja);
-  load_x(0, x1, x2);
+  int cur = -1;
+  if (nl > 0) {
+    cur = member_species(0);
+    load_j(cur, ja);
+    load_x(0, x1, x2);
+  }
   for (int a = 0; a < nl; ++a) {
     bool change = false;
     if (a + 1 < nl) {  // uniform
@@ -136,7 +134,8 @@ __global__ __launch_bounds__(256) void kubo_trace_kernel(int n_atoms, const int6
       v.x += __shfl_xor(v.x, o);
       v.y += __shfl_xor(v.y, o);
     }
-    if (lane == 0) out[3 * m] = v;
+    // no member, no sum: an infinity or NaN of J0 times zero would still be one
+    if (lane == 0) out[3 * m] = nl > 0 ? v : make_double2(0.0, 0.0);
   }
 }
 
