@@ -84,7 +84,7 @@ TRAFFIC = {
     ("split", "fcc4000", 13): {"sha256": "9001bedb113c858cbd9ba443f681c5ea7cc9357d9d5376fc8cf357fbb44d05b4",
                                "alg_bytes_per_launch": 6.9042e10, "bytes_per_launch": 1.1088e11},
     # (the kernels that write the operand pairs, in the same launch: another 2.110e10)
-    ("split", "fcc4000", 19): {"sha256": "e02784e800e1369030382cd349eb6a3704d396d2631616b393e90ac0ae8386ef",
+    ("split", "fcc4000", 19): {"sha256": "6547eadb736cdedadb12405b4117050f7d2e8220d79e6a6d8a9dec513b6a5a27",
                                "alg_bytes_per_launch": 6.9042e10, "bytes_per_launch": 8.6338e+10},
     ("split", "fcc4000", 20): {"sha256": "9001bedb113c858cbd9ba443f681c5ea7cc9357d9d5376fc8cf357fbb44d05b4",
                                "alg_bytes_per_launch": 6.9042e10, "bytes_per_launch": 8.4043e10},
@@ -326,6 +326,34 @@ def gemm_roofline(ctx, precision, workload, tiling, sizes, timed_in):
             "alg_bytes_per_launch": alg_bytes / launches, "fp16_pair_flops_share": share}
 
 
+def library_rates(torch):
+    """Rates of a 1 GiB torch copy and of 8192^3 torch products: twenty calls one after the other (a single product
+    runs at a higher clock), best of three (HIP events)."""
+    def best(call):
+        times = []
+        for _ in range(3):
+            call()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                call()
+            b.record()
+            b.synchronize()
+            times.append(1e-3 * a.elapsed_time(b) / 20)
+        return min(times)
+
+    src = torch.ones(1 << 28, dtype=torch.float32, device="cuda")
+    dst = torch.empty_like(src)
+    out = {"library_copy_1GiB": {"value": 2 * src.numel() * 4 / best(lambda: dst.copy_(src)) / 1e9,
+                                 "unit": "GB/s (read + written)"}}
+    for name, dtype in (("bf16", torch.bfloat16), ("f32", torch.float32), ("f64", torch.float64)):
+        a, b = (torch.randn((8192, 8192), device="cuda").to(dtype) for _ in range(2))
+        c = torch.empty_like(a)
+        out["library_product_8192_%s" % name] = {"value": 2 * 8192.0 ** 3 / best(lambda: torch.mm(a, b, out=c)) / 1e12,
+                                                 "unit": "TFLOP/s"}
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -367,8 +395,8 @@ def main():
                     help="wave workspace as a fraction of free HBM after the inputs are allocated "
                          "(the library's own default is 0.6, which leaves more room for the caller)")
     ap.add_argument("--peak-probe", action="store_true",
-                    help="print the device's sustained MFMA, FP64 FMA and HBM rates (lsms_peak_probe) as one "
-                         "JSON line and exit")
+                    help="print the device's sustained MFMA, FP64 FMA and HBM rates (lsms_peak_probe) and those of "
+                         "a large library copy and of large library products as one JSON line and exit")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="run one 1 GiB device-to-device copy before the timed region (scale for HBM counters)")
     args = ap.parse_args()
@@ -387,6 +415,7 @@ def main():
                  "copy": "GB/s (read + written)", "write": "GB/s", "read": "GB/s"}
         res = {k: {"value": ctx.peak_probe(k), "unit": u} for k, u in units.items()}
         ctx.close()
+        res.update(library_rates(torch))
         print(json.dumps(res), flush=True)
         return
 
