@@ -169,7 +169,8 @@ __device__ inline double2 shfl2(double2 v, int src) { return make_double2(__shfl
 // 16-byte stores at a time, fills the LDS pipe: 150 000 cycles for the 64 columns of 256 FP32
 // rows, 137 000 this way), and every wavefront reads it once, entry q in lane q.
 // Bound by that chain, about 2200 cycles a column, by the update's arithmetic from three row
-// slots on, and for tall panels by the rank-IB updates' traffic.  Leaves are as wide as the
+// slots on, and for tall panels by the rank-IB updates' traffic (320 FP64 systems, three and four row slots: 4.2 and
+// 4.3 TB/s, nearly five times the panels' own bytes, where a copy reaches 5.0).  Leaves are as wide as the
 // registers allow, since every leaf pays once for loading, storing, interchanging the other columns
 // and the rank update.  One panel, on 2 and on 320 systems (us; before: rows exchanged in
 // registers, the moved rows listed by one thread, leaves of 8 and 16): FP64 256 rows 112 / 180
