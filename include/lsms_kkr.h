@@ -396,8 +396,8 @@ int lsms_set_profiling(lsms_ctx* ctx, int on);
  * tilings of the narrow (a panel's 64 columns within its group, K < 64 x group) and wide
  * (K = 64 x group) trailing updates.
  * knob LSMS_TUNE_PANEL_SMALL_ROWS (0 .. 768, default 768): split-mode panels of at most this
- * many rows run in 256-thread workgroups (two jobs per compute unit), taller ones in
- * 512-thread workgroups (one job per compute unit).
+ * many rows run in 256-thread workgroups (two jobs per compute unit; 64 rows of more than 512
+ * systems in one wavefront each), taller ones in 512-thread workgroups (one job per compute unit).
  * For every such choice (and LSMS_TUNE_GEMM_F32), -1 (the initial value) means: the
  * autotuned choice for the wave's padded size (lsms_autotune_kernel), else the library
  * default.  lsms_get_tuning reports the explicit setting (-1 if none), except for

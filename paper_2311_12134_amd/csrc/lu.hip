@@ -1173,6 +1173,11 @@ __global__ __launch_bounds__(256) void tslu_l21_kernel(const JobDesc* jobs, int 
 // workgroups, two per compute unit: 320 panels of 512 rows 176 us against 258 in 512-thread
 // workgroups, of 768 rows 236 against 348 (2 panels: 118 and 116, 157 and 150).  FP64 panels do up to 256
 // rows, where one row slot holds a 32-wide leaf.
+// FP32 panels of 64 rows, more than two per compute unit, take one wavefront each (six per compute unit):
+// bitwise the same, and slower by itself, but 256 threads would go round again.  A solve of one-member
+// systems, 512 of them 350 us against 372 by one wavefront, 600 450 against 409, 2400 1110 against 943, 5000 2136
+// against 1800; of 5000 of n = 144 in the symmetric form, whose every panel has 64 rows, 9.66 ms against 8.75.
+constexpr int MANY_SMALL = 2 * 256;  // of an MI355X's 256 compute units
 template <typename T>
 static void launch_panel(const JobDesc* jobs, int njobs, int k, int left, int rows, T* work, int32_t* piv,
                          int32_t* info, hipStream_t s, int nopiv = 0, int small_rows = PANEL_SMALL_ROWS) {
@@ -1191,10 +1196,12 @@ static void launch_panel(const JobDesc* jobs, int njobs, int k, int left, int ro
   typedef std::integral_constant<int, 8> I8;
   typedef std::integral_constant<int, 16> I16;
   typedef std::integral_constant<int, 32> I32;
+  typedef std::integral_constant<int, 64> P64;
   typedef std::integral_constant<int, 256> P256;
   typedef std::integral_constant<int, 512> P512;
   if constexpr (sizeof(T) == sizeof(float2)) {
     if (rows <= std::min(small_rows, PANEL_SMALL_MAX)) {
+      if (rows <= 64 && njobs > MANY_SMALL) return run(P64{}, I1{}, I32{});
       switch ((rows + 255) / 256) {
         case 1: return run(P256{}, I1{}, I32{});
         case 2: return run(P256{}, I2{}, I32{});

@@ -33,3 +33,20 @@ def test_exact_zero_pivots_are_reported_at_their_column(n, tall_rows):
     # the factors of the regular system: L below the diagonal, U above; the panels' diagonal blocks hold inverses
     f = s.results()[-2].astype(np.complex128)
     assert np.isfinite(f).all()
+
+
+def test_many_systems_as_few():
+    """600 systems in one call, whose panels of 64 rows take one wavefront each, and the same three by themselves."""
+    rng = np.random.default_rng(4)
+    mats = []
+    for n in (64, 128, 192):
+        m = 0.3 * (rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))) / np.sqrt(n)
+        mats.append(m + m.T + np.eye(n))
+    mats[1][70, 70] = mats[1][70, :70] @ np.linalg.solve(mats[1][:70, :70], mats[1][:70, 70])  # nearly singular minor
+    few, many = ik.Systems(mats), ik.Systems(mats * 200)
+    ik.ldlt(few, 64)
+    ik.ldlt(many, 64)
+    want = few.results()
+    assert many.info.cpu().tolist() == few.info.cpu().tolist() * 200
+    for i, got in enumerate(many.results()):
+        assert np.array_equal(got, want[i % 3], equal_nan=True)

@@ -98,6 +98,33 @@ def test_infinite_pivots_in_fp64(ctx, chunk):
         ctx.set_tslu_chunk(2048)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "split"])
+def test_many_small_systems_as_few(ctx, precision):
+    """600 systems of up to 64 rows in one call, whose FP32 panels take one wavefront each, and in two calls: bitwise the
+    same, singular ones and ties among them."""
+    rng = np.random.default_rng(8)
+    mats, rhs = [], []
+    for i in range(600):
+        n = 64 if i % 3 == 0 else int(rng.integers(1, 65))
+        m = rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))
+        if i % 7 == 0:
+            m = rng.integers(-1, 2, (n, n)) + 1j * rng.integers(-1, 2, (n, n))
+        if i % 11 == 0:
+            m[:, rng.integers(n)] = 0
+        mats.append(m.astype(np.complex128))
+        rhs.append(rng.normal(size=(n, 2)) + 1j * rng.normal(size=(n, 2)))
+    x, info = _solve(ctx, mats, rhs, precision)
+    halves = [_solve(ctx, mats[h], rhs[h], precision) for h in (slice(0, 300), slice(300, 600))]
+    assert np.array_equal(info, np.concatenate([h[1] for h in halves])) and (info != 0).any() and (info == 0).any()
+    for a, b in zip(x, halves[0][0] + halves[1][0]):
+        assert np.array_equal(a, b, equal_nan=True)
+    eps = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24
+    for m, b, v, i in zip(mats, rhs, x, info):
+        if i == 0 and np.linalg.matrix_rank(m) == len(m):
+            back = np.linalg.norm(m @ v - b) / (np.linalg.norm(m) * np.linalg.norm(v))
+            assert back <= 10 * np.sqrt(len(m)) * eps, (len(m), back)
+
+
 def test_few_tall_systems_look_ahead_bitwise(ctx):
     """One LIZ of 259 members (n = 4160, tournament panels), where the next group's first panel runs on a stream of
     its own, against graph replay, which keeps one stream."""
